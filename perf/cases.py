@@ -82,7 +82,7 @@ def draw(rng):
                          system=sys_, dt_rule=1, cfl=0.1, oe=rng.choice(["type2", "type2", "type1", "off"]))
         n = 10 * size(40, 600)   # the shock on a cell face
         char = rng.random() < 0.3
-        return _case("run", "shock1d", n, 1, 5 if char else max(k, 4), rng.randrange(60, 240), bc="transmissive", char=char)
+        return _case("run", "shock1d", n, 1, 5 if char else max(k, 5), rng.randrange(60, 240), bc="transmissive", char=char)
     if kind == "table2d":
         n = size(20, 120)
         return _case("run", "diagonal", n, n, k, rng.randrange(10, 60), dt_rule=1, cfl=0.1)
@@ -150,7 +150,7 @@ def _prim(init, system, rng):
                              torch.where(x < -4.0, (2.629369 + du) * one(x), du * one(x)), 0.0 * x,
                              torch.where(x < -4.0, 10.33333 * one(x), one(x)))
     if init == "quadrant":
-        st = [(rng.uniform(0.1, 1.5), rng.uniform(-1.0, 1.0), rng.uniform(-1.0, 1.0), rng.uniform(0.02, 1.5))
+        st = [(rng.uniform(0.2, 1.5), rng.uniform(-0.7, 0.7), rng.uniform(-0.7, 0.7), rng.uniform(0.1, 1.5))
               for _ in range(4)]
 
         def f(x, y):
