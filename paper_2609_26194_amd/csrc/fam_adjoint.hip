@@ -533,7 +533,7 @@ __global__ void __launch_bounds__(256) adj_alpha_part_kernel(AdjMesh m, const do
                                                              double* __restrict__ pv, int* __restrict__ pi) {
   __shared__ double sv[2][4];
   __shared__ int si[2][4];
-  const Euler<2> ph{m.gamma};
+  const Euler<2> ph(m.gamma);
   bool bad = false;
   double vx = -1.0, vy = -1.0;
   int ix = INT_MAX, iy = INT_MAX;
@@ -698,7 +698,7 @@ __global__ void __launch_bounds__(ADJ_T) oe_adj_rec_kernel(AdjMesh m, const doub
     }
   }
   __syncthreads();
-  const Euler<2> ph{m.gamma};
+  const Euler<2> ph(m.gamma);
   bool bad = false;
 #pragma unroll
   for (int t = 0; t < NLP; ++t) {

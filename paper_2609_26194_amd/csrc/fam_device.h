@@ -89,45 +89,44 @@ __host__ __device__ constexpr inline void coeffs2d(const double* u0, const doubl
                  b9 = u1[8];
     const double e1 = u2[0], e2 = u2[1], e3 = u2[2], e5 = u2[4], e7 = u2[6], e8 = u2[7],
                  e9 = u2[8];
-    const double dxx = a4 - 2.0 * a5 + a6, dyy = a2 - 2.0 * a5 + a8;
-    const double cross = a1 - a3 - a7 + a9;
+    // sums, differences and second differences along each patch row (L below, 0
+    // the cell's own, U above), shared by all coefficients: 74 operations for the
+    // 15 coefficients of k = 5 instead of 112 with every formula written out
+    const double sL = a1 + a3, dL = a3 - a1, d0 = a6 - a4, sU = a7 + a9, dU = a9 - a7;
+    const double qL = sL - 2.0 * a2, q0 = (a4 + a6) - 2.0 * a5, qU = sU - 2.0 * a8;
+    const double dyy = (a2 + a8) - 2.0 * a5, cross = dU - dL;
+    const double qd = qU - qL, dd = (dL + dU) - 2.0 * d0;
+    const double sbL = b1 + b3, dbL = b3 - b1, sb0 = b4 + b6, db0 = b6 - b4, sbU = b7 + b9, dbU = b9 - b7;
+    const double sbd = sbL - sbU, dbd = dbL - dbU, sbb = (sbL + sbU) - 2.0 * sb0, dbb = (dbL + dbU) - 2.0 * db0;
+    const double qeL = (e1 + e3) - 2.0 * e2, deL = e3 - e1, qeU = (e7 + e9) - 2.0 * e8, deU = e9 - e7;
+    const double qes = qeL + qeU, qed = qeL - qeU, des = deL + deU, ded = deL - deU, e0d = e2 - e8, e0s = e2 + e8;
     c[0] = a5;
     c[1] = 12.0 * b5;
     c[2] = 12.0 * e5;
-    c[3] = (73.0 / 56.0) * dxx + (135.0 / 28.0) * (b4 - b6);
-    c[4] = (41.0 / 76.0) * cross + (33.0 / 19.0) * (b1 + b3 - b7 - b9 + e1 - e3 + e7 - e9);
-    c[5] = (73.0 / 56.0) * dyy + (135.0 / 28.0) * (e2 - e8);
-    c[6] = (595.0 / 324.0) * (a6 - a4) - (985.0 / 162.0) * (b4 + b6) - (2585.0 / 81.0) * b5;
-    c[7] = (1695.0 / 2128.0) * (-a1 + 2.0 * a2 - a3 + a7 - 2.0 * a8 + a9) +
-           (135.0 / 56.0) * (-b1 + b3 + b7 - b9) +
-           (33.0 / 19.0) * (-e1 + 2.0 * e2 - e3 - e7 + 2.0 * e8 - e9);
-    c[8] = (1695.0 / 2128.0) * (-a1 + a3 + 2.0 * a4 - 2.0 * a6 - a7 + a9) +
-           (33.0 / 19.0) * (-b1 - b3 + 2.0 * b4 + 2.0 * b6 - b7 - b9) +
-           (135.0 / 56.0) * (-e1 + e3 + e7 - e9);
-    c[9] = (595.0 / 324.0) * (a8 - a2) - (985.0 / 162.0) * (e2 + e8) - (2585.0 / 81.0) * e5;
-    const double lap2 = a1 - 2.0 * a2 + a3 - 2.0 * a4 + 4.0 * a5 - 2.0 * a6 + a7 - 2.0 * a8 + a9;
-    c[10] = (59.0 / 56.0) * lap2 +
-            (135.0 / 56.0) * (b1 - b3 - 2.0 * b4 + 2.0 * b6 + b7 - b9 + e1 - 2.0 * e2 + e3 - e7 +
-                              2.0 * e8 - e9);
-    c[11] = (5.0 / 8.0) * (-dxx) + (15.0 / 4.0) * (b6 - b4);
-    c[12] = (5.0 / 38.0) * (-cross) + (30.0 / 19.0) * (-b1 - b3 + b7 + b9);
-    c[13] = (5.0 / 38.0) * (-cross) + (30.0 / 19.0) * (-e1 + e3 - e7 + e9);
-    c[14] = (5.0 / 8.0) * (-dyy) + (15.0 / 4.0) * (e8 - e2);
+    c[3] = (73.0 / 56.0) * q0 - (135.0 / 28.0) * db0;
+    c[4] = (41.0 / 76.0) * cross + (33.0 / 19.0) * (sbd - des);
+    c[5] = (73.0 / 56.0) * dyy + (135.0 / 28.0) * e0d;
+    c[6] = (595.0 / 324.0) * d0 - (985.0 / 162.0) * sb0 - (2585.0 / 81.0) * b5;
+    c[7] = (1695.0 / 2128.0) * qd + (135.0 / 56.0) * dbd - (33.0 / 19.0) * qes;
+    c[8] = (1695.0 / 2128.0) * dd - (33.0 / 19.0) * sbb + (135.0 / 56.0) * ded;
+    c[9] = (595.0 / 324.0) * (a8 - a2) - (985.0 / 162.0) * e0s - (2585.0 / 81.0) * e5;
+    const double lap2 = (qL + qU) - 2.0 * q0;
+    c[10] = (59.0 / 56.0) * lap2 + (135.0 / 56.0) * (qed - dbb);
+    c[11] = (15.0 / 4.0) * db0 - (5.0 / 8.0) * q0;
+    c[12] = -(5.0 / 38.0) * cross - (30.0 / 19.0) * sbd;
+    c[13] = (30.0 / 19.0) * des - (5.0 / 38.0) * cross;
+    c[14] = -(5.0 / 8.0) * dyy - (15.0 / 4.0) * e0d;
     if (K == 6 || full) {
-      c[15] = (35.0 / 36.0) * (a4 - a6) + (77.0 / 18.0) * (b4 + b6) + (133.0 / 9.0) * b5;
-      c[16] = (5.0 / 16.0) * (a1 - 2.0 * a2 + a3 - a7 + 2.0 * a8 - a9) +
-              (15.0 / 8.0) * (b1 - b3 - b7 + b9);
-      c[17] = (5.0 / 38.0) * (a1 - a3 - 2.0 * a4 + 2.0 * a6 + a7 - a9) +
-              (30.0 / 19.0) * (b1 + b3 - 2.0 * b4 - 2.0 * b6 + b7 + b9);
-      c[18] = (5.0 / 38.0) * (a1 - 2.0 * a2 + a3 - a7 + 2.0 * a8 - a9) +
-              (30.0 / 19.0) * (e1 - 2.0 * e2 + e3 + e7 - 2.0 * e8 + e9);
-      c[19] = (5.0 / 16.0) * (a1 - a3 - 2.0 * a4 + 2.0 * a6 + a7 - a9) +
-              (15.0 / 8.0) * (e1 - e3 - e7 + e9);
-      c[20] = (35.0 / 36.0) * (a2 - a8) + (77.0 / 18.0) * (e2 + e8) + (133.0 / 9.0) * e5;
+      c[15] = (77.0 / 18.0) * sb0 + (133.0 / 9.0) * b5 - (35.0 / 36.0) * d0;
+      c[16] = -(5.0 / 16.0) * qd - (15.0 / 8.0) * dbd;
+      c[17] = (30.0 / 19.0) * sbb - (5.0 / 38.0) * dd;
+      c[18] = (30.0 / 19.0) * qes - (5.0 / 38.0) * qd;
+      c[19] = -(5.0 / 16.0) * dd - (15.0 / 8.0) * ded;
+      c[20] = (35.0 / 36.0) * (a2 - a8) + (77.0 / 18.0) * e0s + (133.0 / 9.0) * e5;
     }
     if (full) {
-      c[21] = (5.0 / 16.0) * (-lap2) + (15.0 / 8.0) * (-b1 + b3 + 2.0 * b4 - 2.0 * b6 - b7 + b9);
-      c[22] = (5.0 / 16.0) * (-lap2) + (15.0 / 8.0) * (-e1 + 2.0 * e2 - e3 + e7 - 2.0 * e8 + e9);
+      c[21] = (15.0 / 8.0) * dbb - (5.0 / 16.0) * lap2;
+      c[22] = -(5.0 / 16.0) * lap2 - (15.0 / 8.0) * qed;
     }
   }
 }
@@ -154,28 +153,52 @@ __device__ __forceinline__ void coeffs1d(double u0m, double u00, double u0p, dou
   }
 }
 
-// 1/x from the hardware reciprocal estimate refined by two Newton steps
-// (relative error within a few units in the last place; not IEEE division)
+// 1/x from the hardware reciprocal estimate r (relative error at most 4.6e-8) and
+// the remainder e = 1 - x r: 1/x = r / (1 - e) = r + r (e + e^2) up to r e^3, below
+// 1e-22 of it, so the result is within rounding of 1/x (not IEEE division)
 __device__ __forceinline__ double rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// a value that the compiler computes here, for all active lanes: it would move a
+// division that only some lanes' selects use into a branch of its own
+__device__ __forceinline__ double here(double x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// a value that is the same in every lane, moved to scalar registers
+__device__ __forceinline__ double uniform(double x) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(x)));
 }
 
 // ---------------------------------------------------------------------------
 // Physics
 // ---------------------------------------------------------------------------
+//
+// flux: f_d(u).  The 2D stage kernel takes a face flux apart into the shares of its
+// two sides, F = 1/2 (f(u-) + alpha u-) + 1/2 (f(u+) - alpha u+): face() is one
+// side's f_d(u) + a u with a = +-alpha (the 1/2 is applied to the residual).
+// volume() adds a point of weight w to the sums of the volume quadrature and
+// volume_sums() turns them into V1, V2, the averages of f_1, f_2; the means of
+// the components themselves are the average (the 4 x 4 rule is exact for p_k).
 struct Advection {
   static constexpr int NC = 1;
   double ax, ay;
+  struct Volume {};
+  __device__ __forceinline__ void face(int d, const double* u, double a, double* g) const {
+    g[0] = ((d == 0 ? ax : ay) + a) * u[0];
+  }
+  __device__ __forceinline__ void volume(const double*, double, Volume&) const {}
+  __device__ __forceinline__ void volume_sums(const double* mean, const Volume&, double* V1, double* V2) const {
+    V1[0] = ax * mean[0];
+    V2[0] = ay * mean[0];
+  }
   __device__ __forceinline__ void flux(int d, const double* u, double* f) const {
     f[0] = (d == 0 ? ax : ay) * u[0];
-  }
-  __device__ __forceinline__ void flux2(const double* u, double* f1, double* f2) const {
-    f1[0] = ax * u[0];
-    f2[0] = ay * u[0];
   }
   __device__ __forceinline__ double speed(int d, const double* u, bool& bad) const {
     bad |= !(u[0] == u[0]);
@@ -186,12 +209,18 @@ struct Advection {
 struct Burgers {
   static constexpr int NC = 1;
   double ax, ay;
+  struct Volume {
+    double s;
+  };
+  __device__ __forceinline__ void face(int, const double* u, double a, double* g) const {
+    g[0] = fma(0.5, u[0], a) * u[0];
+  }
+  __device__ __forceinline__ void volume(const double* u, double w, Volume& V) const { V.s = fma(w * u[0], u[0], V.s); }
+  __device__ __forceinline__ void volume_sums(const double*, const Volume& V, double* V1, double* V2) const {
+    V1[0] = V2[0] = 0.5 * V.s;
+  }
   __device__ __forceinline__ void flux(int, const double* u, double* f) const {
     f[0] = 0.5 * u[0] * u[0];
-  }
-  __device__ __forceinline__ void flux2(const double* u, double* f1, double* f2) const {
-    f1[0] = 0.5 * u[0] * u[0];
-    f2[0] = f1[0];
   }
   __device__ __forceinline__ double speed(int, const double* u, bool& bad) const {
     bad |= !(u[0] == u[0]);
@@ -203,11 +232,13 @@ struct Burgers {
 template <int DIM>
 struct Euler {
   static constexpr int NC = DIM + 2;
-  double g;
+  double g, g1, kh;   // gamma, gamma - 1, -(gamma - 1)/(2 gamma), in scalar registers
+  __device__ __forceinline__ explicit Euler(double gamma)
+      : g(gamma), g1(uniform(gamma - 1.0)), kh(uniform(-0.5 * (gamma - 1.0) / gamma)) {}
   __device__ __forceinline__ double pressure(const double* u, double inv_rho) const {
     double ke = u[1] * u[1];
     if constexpr (DIM == 2) ke += u[2] * u[2];
-    return (g - 1.0) * (u[NC - 1] - 0.5 * ke * inv_rho);
+    return g1 * (u[NC - 1] - 0.5 * ke * inv_rho);
   }
   __device__ __forceinline__ void flux(int d, const double* u, double* f) const {
     const double inv = rcp(u[0]);
@@ -219,26 +250,47 @@ struct Euler {
     f[1 + d] += p;
     f[NC - 1] = (u[NC - 1] + p) * vel;
   }
-  // both directional fluxes at one point (shared 1/rho and pressure)
-  __device__ __forceinline__ void flux2(const double* u, double* f1, double* f2) const {
+  // sums over the volume points of u_x^2 rho, u_y^2 rho, u_x u_y rho and
+  // (E + p) u_x, (E + p) u_y divided by gamma
+  struct Volume {
+    double xx, yy, xy, hx, hy;
+  };
+  __device__ __forceinline__ void face(int d, const double* u, double a, double* o) const {
     const double inv = rcp(u[0]);
-    const double p = pressure(u, inv);
-    const double vx = u[1] * inv;
-    const double vy = u[DIM == 2 ? 2 : 1] * inv;
-    f1[0] = u[1];
-    f1[1] = u[1] * vx + p;
-    if constexpr (DIM == 2) {
-      f1[2] = u[2] * vx;
-      f2[0] = u[2];
-      f2[1] = u[1] * vy;
-      f2[2] = u[2] * vy + p;
-      f2[3] = (u[3] + p) * vy;
-    }
-    f1[NC - 1] = (u[NC - 1] + p) * vx;
+    const double ke = fma(u[2], u[2], u[1] * u[1]);
+    const double p = g1 * fma(-0.5, ke * inv, u[3]);
+    const double vel = u[1 + d] * inv, va = vel + a;
+    o[0] = fma(a, u[0], u[1 + d]);
+    o[1 + d] = fma(u[1 + d], va, p);
+    o[2 - d] = u[2 - d] * va;
+    o[3] = fma(u[3], va, p * vel);
+  }
+  __device__ __forceinline__ void volume(const double* u, double w, Volume& V) const {
+    const double inv = rcp(u[0]);
+    const double ke = fma(u[2], u[2], u[1] * u[1]);
+    const double h = fma(kh, ke * inv, u[3]);   // (E + p) / gamma
+    const double wi = w * inv;
+    const double vx = u[1] * wi, vy = u[2] * wi;
+    V.xx = fma(u[1], vx, V.xx);
+    V.xy = fma(u[1], vy, V.xy);
+    V.yy = fma(u[2], vy, V.yy);
+    V.hx = fma(h, vx, V.hx);
+    V.hy = fma(h, vy, V.hy);
+  }
+  __device__ __forceinline__ void volume_sums(const double* mean, const Volume& V, double* V1, double* V2) const {
+    const double p = g1 * fma(-0.5, V.xx + V.yy, mean[3]);
+    V1[0] = mean[1];
+    V1[1] = V.xx + p;
+    V1[2] = V.xy;
+    V1[3] = g * V.hx;
+    V2[0] = mean[2];
+    V2[1] = V.xy;
+    V2[2] = V.yy + p;
+    V2[3] = g * V.hy;
   }
   // spectral radius |u_d| + c at a cell average; flags rho <= 0, p <= 0, NaN
   __device__ __forceinline__ double speed(int d, const double* u, bool& bad) const {
-    const double inv = 1.0 / u[0];
+    const double inv = rcp(u[0]);
     const double p = pressure(u, inv);
     bad |= !(u[0] > 0.0) || !(p > 0.0);
     return fabs(u[1 + d] * inv) + sqrt(g * p * inv);
@@ -268,8 +320,12 @@ __device__ __forceinline__ void atomic_max_nonneg(double* addr, double v) {
 // ghost-cell index map: periodic wrap or transmissive clamp
 __device__ __forceinline__ int ghost(int i, int n, int bc) {
   if (bc == 0) {
-    i %= n;
-    return i < 0 ? i + n : i;
+    i += i < 0 ? n : i >= n ? -n : 0;
+    if (__any((unsigned)i >= (unsigned)n)) {   // beyond one period (a strip wider than the mesh)
+      i %= n;
+      i += i < 0 ? n : 0;
+    }
+    return i;
   }
   return i < 0 ? 0 : (i >= n ? n - 1 : i);
 }

@@ -16,48 +16,38 @@ __device__ __forceinline__ constexpr double qx(int q) {
   return q == 0 ? -GS1 : q == 1 ? -GS0 : q == 2 ? GS0 : GS1;
 }
 
-// even / odd partial contractions over the y-degree: E[m][w], O[m][w] at
-// w = 0 (GS0), 1 (GS1), 2 (1/2), 3 (0; even part only)
-template <int NCF, int MD>
-__device__ __forceinline__ void contract_y(const double* c, double (&E)[MD + 1][4],
-                                           double (&O)[MD + 1][3]) {
+// index of the basis function L_a(xi) L_b(eta) among those of complete degree k - 1
+__host__ __device__ constexpr int basis_index(int a, int b) {
+  for (int l = 0; l < 23; ++l)
+    if (AX[l] == a && AY[l] == b) return l;
+  return -1;
+}
+
+// the polynomial in xi that p_k is on the line eta = sy * node(gy) (node 2 = 1/2):
+// Q[m] is its coefficient of L_m.  The odd terms come first, so that the compiler
+// finds nothing to keep for the opposite line.
+template <int K>
+__device__ __forceinline__ void line_y(const double* c, int gy, double sy, double* Q) {
 #pragma unroll
-  for (int m = 0; m <= MD; ++m) {
+  for (int m = 0; m < K; ++m) {
+    Q[m] = c[basis_index(m, 0)];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) E[m][w] = 0.0;
-#pragma unroll
-    for (int w = 0; w < 3; ++w) O[m][w] = 0.0;
-  }
-#pragma unroll
-  for (int l = 0; l < NCF; ++l) {
-    const int m = AX[l], b = AY[l];
-    if (b % 2 == 0) {
-#pragma unroll
-      for (int w = 0; w < 3; ++w) E[m][w] = fma(c[l], legn(b, w), E[m][w]);
-      E[m][3] = fma(c[l], leg(b, 0.0), E[m][3]);
-    } else {
-#pragma unroll
-      for (int w = 0; w < 3; ++w) O[m][w] = fma(c[l], legn(b, w), O[m][w]);
-    }
+    for (int b = 1; b + m < K; ++b) Q[m] = fma(c[basis_index(m, b)], (b & 1) ? sy * legn(b, gy) : legn(b, gy), Q[m]);
   }
 }
 
-// p(xi, eta) with xi = sx * node(gx), eta = sy * node(gy); node 2 = 1/2
+// its values at xi = +X and -X, X = node(gx): one even and one odd part,
+// L_3(X) = X (X^2 - 3/20), L_5(X) likewise, so X enters with the last operation
 template <int MD>
-__device__ __forceinline__ double eval_pt(const double (&E)[MD + 1][4], const double (&O)[MD + 1][3],
-                                          int gx, double sx, int gy, double sy) {
-  double ev = 0.0, od = 0.0;
-#pragma unroll
-  for (int m = 0; m <= MD; ++m) {
-    const double Qm = E[m][gy] + sy * O[m][gy];
-    if (m % 2 == 0)
-      ev = fma(legn(m, gx), Qm, ev);
-    else
-      od = fma(legn(m, gx), Qm, od);
-  }
-  return ev + sx * od;
+__device__ __forceinline__ void pair_x(const double* Q, int gx, double& vp, double& vm) {
+  const double X = legn(1, gx);
+  double ev = fma(Q[2], legn(2, gx), Q[0]), od = Q[1];
+  if constexpr (MD >= 4) ev = fma(Q[4], legn(4, gx), ev);
+  if constexpr (MD >= 3) od = fma(Q[3], legn(3, gx) / X, od);
+  if constexpr (MD >= 5) od = fma(Q[5], legn(5, gx) / X, od);
+  vp = fma(X, od, ev);
+  vm = fma(-X, od, ev);
 }
-
 
 // Stencil slots that the reconstruction reads: slot 0..8 the averages of the
 // 3x3 patch, 9..17 its x-moments, 18..26 its y-moments (patch index b*3 + a).

@@ -10,10 +10,11 @@
 namespace fam {
 
 constexpr int STRIP = 60;   // output columns per 2D strip (one wavefront)
-// waves of the RK stage kernel per SIMD that its register and LDS budget allows
-#ifndef FAM_STAGE_WAVES
-#define FAM_STAGE_WAVES 1
-#endif
+// waves of the RK stage kernel per SIMD that its registers and LDS allow (order k,
+// nc components, reconstruction in characteristic variables)
+__host__ __device__ constexpr int stage_waves(int k, int nc, bool charv) {
+  return nc == 1 ? 4 : (k >= 6 || charv) ? 1 : 2;
+}
 
 struct PhysParams {
   double gamma, ax, ay;
@@ -64,8 +65,9 @@ struct StageArgs {
   // its count of such cells to tile_work
   const int* tile_perm;
   int* tile_work;
-  // single-instance limiter launches over a segment list: cycles spent on each
-  // row of each strip, row_cost[strip * ny + row] (NULL: not recorded)
+  // single-instance limiter launches over a segment list: the cost of each row of
+  // each strip in rows without limiter work, row_cost[strip * ny + row] (NULL: not
+  // recorded)
   float* row_cost;
 };
 

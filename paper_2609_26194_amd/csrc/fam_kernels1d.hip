@@ -42,7 +42,7 @@ __device__ __forceinline__ Advection make_phys1<Advection>(const PhysParams& pp)
 template <>
 __device__ __forceinline__ Burgers make_phys1<Burgers>(const PhysParams& pp) { return Burgers{pp.ax, pp.ay}; }
 template <>
-__device__ __forceinline__ Euler<1> make_phys1<Euler<1>>(const PhysParams& pp) { return Euler<1>{pp.gamma}; }
+__device__ __forceinline__ Euler<1> make_phys1<Euler<1>>(const PhysParams& pp) { return Euler<1>(pp.gamma); }
 
 struct Tile1 {
   double u[NPL1][T1 + 2];   // cells i0-2 .. i0+255

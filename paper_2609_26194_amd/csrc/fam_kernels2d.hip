@@ -5,10 +5,12 @@
 // columns); lanes 1 and 62 are ring columns whose traces feed the strip's two
 // boundary faces; lanes 0 and 63 only load.  The wave marches upwards over the
 // rows j0-1 .. j0+H (the first and last are ring rows), keeping a rolling window
-// of three state rows (12 planes x 64 columns) in LDS.  Every face flux is evaluated exactly once per strip:
-//   x-faces: a lane's right trace is passed to the right neighbour lane by a
-//            cross-lane shuffle, and the resulting face flux is passed back;
-//   y-faces: the top trace of row r is kept in registers for row r+1.
+// of three state rows (12 planes x 64 columns) in LDS.  Every face flux is evaluated
+// exactly once per strip:
+//   x-faces: a lane's share of its right face's flux, 1/2 (f(u) + alpha u), is
+//            passed to the right neighbour lane by a cross-lane shift, and the
+//            resulting face flux is passed back;
+//   y-faces: a row's share of its top face's flux is kept for the next row.
 // The residual of a cell is complete one row later (after its top face), when
 // the Shu-Osher update writes the stage result.
 //
@@ -43,17 +45,13 @@ namespace fam {
 #define FAM_OE_WAVES 1
 #endif
 // occupancy targets (waves per SIMD) handed to the register allocator
-#define FAM_STAGE_ATTR __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FAM_STAGE_WAVES)))
+#define FAM_STAGE_ATTR(K, CHAR) __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(stage_waves(K, P::NC, CHAR))))
 #define FAM_OE_ATTR __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FAM_OE_WAVES)))
 
-// keeps the scheduler from hoisting the next component's LDS reads above this
-// point (bounds the number of live stencil values); used between the OE kernel's
-// per-component passes (the stage kernels schedule faster without it)
-#ifndef FAM_NO_FENCE
+// keeps the scheduler from moving work across this point, which bounds the number
+// of live values: between the OE kernel's per-component passes and between the
+// parts of a stage row (recon of a component, a line of points, a face)
 #define FAM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
-#else
-#define FAM_SCHED_FENCE() ((void)0)
-#endif
 
 // ---------------------------------------------------------------------------
 // Optional positivity limiter (Euler): the reconstruction p is replaced by
@@ -69,8 +67,9 @@ __device__ __forceinline__ double smallest_root_unit(double a, double b, double 
   const double disc = fmax(b * b - 4.0 * a * c, 0.0);
   const double sq = sqrt(disc);
   const double q = -0.5 * (b + (b >= 0.0 ? sq : -sq));
-  double r1 = (a == 0.0) ? 2.0 : q / a;
-  double r2 = c / (q == 0.0 ? 1.0 : q);
+  double r1 = here(q / (a == 0.0 ? 1.0 : a));
+  r1 = a == 0.0 ? 2.0 : r1;
+  double r2 = here(c / (q == 0.0 ? 1.0 : q));
   if (!(r1 > 0.0 && r1 <= 1.0)) r1 = 2.0;
   if (!(r2 > 0.0 && r2 <= 1.0)) r2 = 2.0;
   const double r = fmin(r1, r2);
@@ -95,65 +94,64 @@ __device__ __forceinline__ double half_wave_min(double v) {
   return fmin(v, __shfl_xor(v, 16, 64));
 }
 
-// LDS staging of the limiter's exact test: up to CHUNK cells of a wave at a time
-// (16; 8 at k = 6, whose kernels also keep their carried traces in LDS and must
-// still fit four blocks per CU)
-template <int K>
-struct PPStage {
-  static constexpr int CHUNK = K == 6 ? 8 : 16;
-  double cf[CHUNK][4 * ncoef2d(K) + 1];   // coefficients of the 4 components, eps
-  double th[CHUNK][2];
-  int nwork;                               // cells of this tile that needed the exact test
-};
+using ScratchDouble = __attribute__((address_space(5))) double;
 
-// Called by all 64 lanes of the wave (uniform control flow).  Each lane first
-// runs a cheap sufficient test; the few cells that fail it (near
-// discontinuities) are then tested exactly and, where needed, limited: their
-// coefficients go to LDS, and each half of the wave takes one cell, lane l
-// evaluating flux point l mod 32, so a cell costs the wave a few dozen
-// instructions instead of a divergent 32-point loop.
-template <int K, int NCF, int MD, class P>
-__device__ __forceinline__ void pp_limiter(const P& phys, double (&cf)[P::NC][NCF], bool& bad, int lane,
-                                           PPStage<K>& S) {
+// The limiter's cheap sufficient test, by every lane on its own cell: the mask of
+// the lanes whose cell needs the exact test, and eps.
+template <int K, int NCF, class P>
+__device__ __forceinline__ unsigned long long pp_cheap_test(const P& phys, const double (&cf)[P::NC][NCF], bool& bad,
+                                                            int lane, double& eps) {
   constexpr int NC = P::NC;
   if constexpr (NC != 4) {
-    return;
+    return 0;
   } else {
     const double g = phys.g;
     double avg[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) avg[c] = cf[c][0];
-    const double inv = 1.0 / avg[0];
+    const double inv = rcp(avg[0]);
     const double pa = phys.pressure(avg, inv);
     const bool adm = (avg[0] > 0.0) && (pa > 0.0);
-    if (!adm) bad = true;
-    const double eps = fmin(fmin(avg[0], pa), 1e-13);
-    // cheap sufficient test: every basis function is bounded by its value at the
-    // cell corner (|L_m| <= L_m(1/2) on [-1/2, 1/2]), which bounds each
-    // component's deviation from its average; if density and the pressure lower
-    // bound built from those deviations stay above eps (with a rounding margin),
-    // no point can violate and the limiter is the identity.
-    bool need = false;
-    if (adm && lane >= 1 && lane <= LANES - 2) {
-      double dev[NC];
+    bad |= !adm;
+    eps = fmin(fmin(avg[0], pa), 1e-13);
+    // every basis function is bounded by its value at the cell corner
+    // (|L_m| <= L_m(1/2) on [-1/2, 1/2]), which bounds each component's deviation
+    // from its average; if density and the pressure lower bound built from those
+    // deviations stay above eps (with a rounding margin), no point can violate and
+    // the limiter is the identity.
+    double dev[NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        dev[c] = 0.0;
+    for (int c = 0; c < NC; ++c) {
+      dev[c] = 0.0;
 #pragma unroll
-        for (int l = 1; l < NCF; ++l) dev[c] = fma(fabs(cf[c][l]), leg(AX[l], 0.5) * leg(AY[l], 0.5), dev[c]);
-      }
-      const double rlo = avg[0] - dev[0];
-      const double mm = fabs(avg[1]) + dev[1], nn = fabs(avg[2]) + dev[2];
-      const double margin = 1e-12 * (avg[0] + dev[0] + fabs(avg[3]) + dev[3]);
-      need = true;
-      if (rlo > eps + margin) {
-        const double plo = (g - 1.0) * (avg[3] - dev[3] - 0.5 * (mm * mm + nn * nn) / rlo);
-        if (plo > eps + margin) need = false;
-      }
+      for (int l = 1; l < NCF; ++l) dev[c] = fma(fabs(cf[c][l]), leg(AX[l], 0.5) * leg(AY[l], 0.5), dev[c]);
     }
-    unsigned long long todo = __ballot(need);
-    if (todo == 0) return;
-    if (lane == 0) S.nwork += __popcll(todo);
+    const double rlo = avg[0] - dev[0];
+    const double mm = fabs(avg[1]) + dev[1], nn = fabs(avg[2]) + dev[2];
+    const double lim = eps + 1e-12 * (avg[0] + dev[0] + fabs(avg[3]) + dev[3]);
+    const double plo = (g - 1.0) * (avg[3] - dev[3] - 0.5 * (mm * mm + nn * nn) * rcp(rlo));
+    const bool need = adm & (lane >= 1) & (lane <= LANES - 2) & !((rlo > lim) & (plo > lim));
+    return __ballot(need);
+  }
+}
+
+// The exact test, called by all 64 lanes of the wave for the few cells (near
+// discontinuities) that fail the cheap one: each half of the wave takes one of them
+// at a time, lane l evaluating flux point l mod 32 of it, so a pair of cells costs
+// the wave a few hundred instructions instead of a divergent 32-point loop.  The
+// coefficients come from the cell's own lane by ds_bpermute (122 per pair); staged
+// in LDS they took 2 KB per wave and the launch 412 us instead of 391 (2048^2, k = 5).
+template <int K, int NCF, int MD, class P>
+__device__ __forceinline__ void pp_exact(const P& phys, double (&cf)[P::NC][NCF], unsigned long long todo, double eps,
+                                         int lane, int& nwork) {
+  constexpr int NC = P::NC;
+  if constexpr (NC == 4) {
+    // the lane number and gamma are hidden from the optimiser here: it would
+    // otherwise compute what depends on them alone (phi, masks, addresses) before
+    // the row loop and hold its registers through every row
+    double g = phys.g;
+    asm volatile("" : "+v"(lane), "+v"(g));
+    if (lane == 0) nwork += __popcll(todo);
     // this lane's flux point: right face (1/2, eta_g), left face (-1/2, eta_g),
     // top face (xi_g, 1/2), bottom face (xi_g, -1/2), volume (xi_a, eta_b) at
     // 16 + 4 b + a
@@ -165,121 +163,179 @@ __device__ __forceinline__ void pp_limiter(const P& phys, double (&cf)[P::NC][NC
     else if (pt < 12) { px = nd[pt - 8]; py = 0.5; }
     else if (pt < 16) { px = nd[pt - 12]; py = -0.5; }
     else { px = nd[(pt - 16) & 3]; py = nd[(pt - 16) >> 2]; }
-    double phi[NCF];
+    double lx[MD + 1], ly[MD + 1];
 #pragma unroll
-    for (int l = 0; l < NCF; ++l) phi[l] = leg(AX[l], px) * leg(AY[l], py);
+    for (int m = 1; m <= MD; ++m) {
+      lx[m] = leg(m, px);
+      ly[m] = leg(m, py);
+    }
     const double kk = 2.0 / (g - 1.0);
     double th1 = 1.0, th2 = 1.0;
-    while (todo) {
-      // the next (up to) CHUNK cells
-      unsigned long long chunk = 0, rest = todo;
-      int nchunk = 0;
-      while (rest && nchunk < PPStage<K>::CHUNK) {
-        chunk |= rest & (~rest + 1ull);
-        rest &= rest - 1ull;
-        ++nchunk;
-      }
-      todo = rest;
-      const bool mine = (chunk >> lane) & 1ull;
-      const int slot = __popcll(chunk & ((1ull << lane) - 1ull));
-      if (mine) {
+    do {
+      // the next two cells (an odd count: both halves take the last one)
+      const int la = __ffsll((long long)todo) - 1;
+      todo &= todo - 1ull;
+      const int lb = todo ? __ffsll((long long)todo) - 1 : la;
+      todo &= todo - 1ull;
+      const int src = half ? lb : la;
+      double v[NC], a[NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+      for (int c = 0; c < NC; ++c) {
+        v[c] = 0.0;
 #pragma unroll
-          for (int l = 0; l < NCF; ++l) S.cf[slot][c * NCF + l] = cf[c][l];
-        S.cf[slot][NC * NCF] = eps;
-      }
-      __syncthreads();
-      for (int p = 0; p < nchunk; p += 2) {
-        const int cell = min(p + half, nchunk - 1);   // an odd count: both halves take the last cell
-        const double* C = S.cf[cell];
-        double v[NC], a[NC];
+        for (int b = MD; b >= 0; --b) {
+          double x = __shfl(cf[c][basis_index(0, b)], src);
+          if (b == 0) a[c] = x;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          v[c] = 0.0;
-#pragma unroll
-          for (int l = 0; l < NCF; ++l) v[c] = fma(C[c * NCF + l], phi[l], v[c]);
-          a[c] = C[c * NCF];
+          for (int m = 1; m + b <= MD; ++m) x = fma(__shfl(cf[c][basis_index(m, b)], src), lx[m], x);
+          v[c] = b > 0 ? fma(x, ly[b], v[c]) : v[c] + x;
         }
-        const double e = C[NC * NCF];
-        // density: theta1 from the minimum over the 32 points
-        const double rmin = half_wave_min(v[0]);
-        const double t1 = rmin < e ? (a[0] - e) / (a[0] - rmin) : 1.0;
-        // pressure along avg -> density-limited point value
-        const double rho0 = a[0], m0 = a[1], n0 = a[2], E0 = a[3];
-        const double w0 = rho0 + t1 * (v[0] - rho0);
-        const double w[4] = {w0, v[1], v[2], v[3]};
-        const double pw = phys.pressure(w, 1.0 / w0);
-        double t2 = 1.0;
-        if (pw < e) {
-          const double qc = 2.0 * rho0 * E0 - (m0 * m0 + n0 * n0) - kk * e * rho0;
-          const double rd = w0 - rho0, md = w[1] - m0, nd_ = w[2] - n0, Ed = w[3] - E0;
-          const double qa = 2.0 * rd * Ed - (md * md + nd_ * nd_);
-          const double qb = 2.0 * (rho0 * Ed + rd * E0) - 2.0 * (m0 * md + n0 * nd_) - kk * e * rd;
-          t2 = smallest_root_unit(qa, qb, qc);
-        }
-        t2 = half_wave_min(t2);
-        if (pt == 0) {
-          S.th[cell][0] = t1;
-          S.th[cell][1] = t2;
-        }
+        FAM_SCHED_FENCE();
       }
-      __syncthreads();
-      if (mine) {
-        th1 = S.th[slot][0];
-        th2 = S.th[slot][1];
+      const double e = __shfl(eps, src);
+      // density: theta1 from the minimum over the 32 points
+      const double rmin = half_wave_min(v[0]);
+      const double tr = here((a[0] - e) / (a[0] - rmin));
+      const double t1 = rmin < e ? tr : 1.0;
+      // pressure along avg -> density-limited point value
+      const double rho0 = a[0], m0 = a[1], n0 = a[2], E0 = a[3];
+      const double w0 = rho0 + t1 * (v[0] - rho0);
+      const double w[4] = {w0, v[1], v[2], v[3]};
+      const double pw = P(g).pressure(w, rcp(w0));
+      double t2 = 1.0;
+      if (__any(pw < e)) {   // for all lanes: no divergent code where the registers are full
+        const double qc = 2.0 * rho0 * E0 - (m0 * m0 + n0 * n0) - kk * e * rho0;
+        const double rd = w0 - rho0, md = w[1] - m0, nd_ = w[2] - n0, Ed = w[3] - E0;
+        const double qa = 2.0 * rd * Ed - (md * md + nd_ * nd_);
+        const double qb = 2.0 * (rho0 * Ed + rd * E0) - 2.0 * (m0 * md + n0 * nd_) - kk * e * rd;
+        const double root = here(smallest_root_unit(qa, qb, qc));
+        t2 = pw < e ? root : 1.0;
       }
-      __syncthreads();
-    }
-    if (th1 < 1.0 || th2 < 1.0) {
-      const double t0 = th1 * th2;
+      t2 = half_wave_min(t2);
+      // each half's results (the same in all its lanes) go to its cell's lane
+      const double t1b = __shfl(t1, 32), t2b = __shfl(t2, 32);
+      const double t1a = __shfl(t1, 0), t2a = __shfl(t2, 0);
+      th1 = lane == la ? t1a : lane == lb ? t1b : th1;
+      th2 = lane == la ? t2a : lane == lb ? t2b : th2;
+    } while (todo);
+    if (__any(th1 < 1.0 || th2 < 1.0)) {
+      const double t0 = th1 * th2;   // a factor of one changes nothing
 #pragma unroll
-      for (int l = 1; l < NCF; ++l) cf[0][l] *= t0;
+      for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int c = 1; c < NC; ++c)
-#pragma unroll
-        for (int l = 1; l < NCF; ++l) cf[c][l] *= th2;
+        for (int l = 1; l < NCF; ++l) cf[c][l] *= c == 0 ? t0 : th2;
     }
   }
 }
 
+// cost of a row with n cells tested exactly, in rows without any: ROW_TEST +
+// ROW_CELL n.  Measured launch times at 2048^2 (k = 5, four-quadrant data), segment
+// list cut by it: 391 us; with 1.3 + 0.1 n 430 us, with 1.5 + 0.2 n 402 us.  (Cycles
+// read from the clock, as the list was cut before, do not converge with two waves
+// on a SIMD: a row's cycles depend on what the other wave does meanwhile, and the
+// segments of one launch took from 164 to 657 us.)
+constexpr float ROW_TEST = 1.8f, ROW_CELL = 0.15f;
+
+// ---------------------------------------------------------------------------
+// Registers and LDS of a stage wave.  What bounds the kernel is the issue of vector
+// instructions (about 2150 per row of 64 cells at k = 5, 1670 of them FP64), so it
+// is written for few of them and for a second wave on the SIMD to fill the gaps:
+// two waves have 256 registers and 20 KB of LDS each.  k = 3..5 fit without spilling
+// (k = 5: 120 registers of coefficients, 40 carried from row to row), because rows
+// go to LDS past the registers and each line's points are used as soon as they are
+// evaluated.  A single spill in the row's second half is expensive: its reload waits
+// for the row prefetch issued before it (33 of them made the kernel 1.5x slower).
+// k = 6 (168 registers of coefficients) and the characteristic variables run one
+// wave per SIMD and use its 40 KB of LDS instead: what a row hands to the next (20
+// values per lane) and the row of the step's start wait there, not in registers.
+// Stage launch at 2048^2, k = 5, no limiter: 486 us with one wave per SIMD and 3140
+// instructions a row (traces of both sides of a face exchanged, written-out
+// coefficient formulas), 430 us with this arithmetic, 385-397 us with two waves.
+// With the limiter (four-quadrant data): 483 us before, 391 us.
+// ---------------------------------------------------------------------------
+template <int K, int NC, bool CHAR>
+__host__ __device__ constexpr bool rich_lds() { return stage_waves(K, NC, CHAR) == 1; }
+
+template <bool ON, int NPLU>
+struct StageU0 {
+  alignas(16) double v[NPLU * LANES];    // row of the step's start that the next iteration finishes
+};
+template <int NPLU>
+struct StageU0<false, NPLU> {};
+template <bool ON>
+struct StageCarry {
+  double2 t[4][LANES];                   // [component]: share of the face above, mean and moment
+  double2 y[6][LANES];                   // residual without the top face: [component]: m = 0, 1; [4], [5]: m = 2
+};
+template <>
+struct StageCarry<false> {};
+
+// references to a wave's LDS objects.  They are separate variables, so that the
+// compiler knows which of them a row on its way to LDS may touch, and waits for it
+// at no other's accesses.
+template <int K, int NC, bool CHAR>
+struct StageShared {
+  Window<3 * NC>& W;
+  StageCarry<rich_lds<K, NC, CHAR>()>& cy;
+  StageU0<rich_lds<K, NC, CHAR>(), 3 * NC>& u0;
+  int& nwork;   // cells of this tile that needed the limiter's exact test
+};
+#define FAM_STAGE_SHARED(K, NC, CHAR)                         \
+  __shared__ Window<3 * NC> s_W;                              \
+  __shared__ StageCarry<rich_lds<K, NC, CHAR>()> s_cy;        \
+  __shared__ StageU0<rich_lds<K, NC, CHAR>(), 3 * NC> s_u0;   \
+  __shared__ int s_nwork;                                     \
+  StageShared<K, NC, CHAR> S { s_W, s_cy, s_u0, s_nwork }
+
 // ---------------------------------------------------------------------------
 // stage tile
 // ---------------------------------------------------------------------------
-// The values a row hands to the next (its top traces, the bottom states of the
-// next y-face, and its residual without the top face) stay in registers, except
-// for the Euler equations at k = 6, whose 4 x 21 coefficients leave no room for
-// them: there each lane keeps its own column of them in LDS.
-template <int K, int NC>
-__host__ __device__ constexpr bool carry_in_lds() { return K == 6 && NC == 4; }
+// sums of the share g = f_2(u) + a u over the four points of the face y = sy/2:
+// Gb = sum_q w_q g, Gt = sum_q w_q xi_q g
+template <int K, int NCF, class P>
+__device__ __forceinline__ void yface_sums(const P& phys, const double (&cf)[P::NC][NCF], double sy, double a,
+                                           double (&Gb)[P::NC], double (&Gt)[P::NC]) {
+  constexpr int NC = P::NC, MD = maxdeg(K);
+  double up[2][NC], um[2][NC];   // values at +xi and -xi of the inner and the outer node
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    double Q[MD + 1];
+    line_y<K>(cf[c], 2, sy, Q);
+    pair_x<MD>(Q, 0, up[0][c], um[0][c]);
+    pair_x<MD>(Q, 1, up[1][c], um[1][c]);
+    Gb[c] = Gt[c] = 0.0;
+  }
+  FAM_SCHED_FENCE();
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    const double w = n == 0 ? GW0 : GW1, x = n == 0 ? GS0 : GS1;
+    double gp[NC], gm[NC];
+    phys.face(1, up[n], a, gp);
+    phys.face(1, um[n], a, gm);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      Gb[c] = fma(w, gp[c] + gm[c], Gb[c]);
+      Gt[c] = fma(w * x, gp[c] - gm[c], Gt[c]);
+    }
+  }
+}
 
-template <bool ON>
-struct StageCarry {
-  double top[16][LANES];    // [component * 4 + point][lane]
-  double part[NPL][LANES];  // [component * 3 + moment][lane]
-};
-template <>
-struct StageCarry<false> {
-  char unused;
-};
 template <int K, class P, bool PP, bool DMR = false, bool CHAR = false>
 __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, int i0, int j0, int H,
-                           Window& W, PPStage<K>& PS, StageCarry<carry_in_lds<K, P::NC>()>& T, double& amax_x,
-                           double& amax_y, bool& bad) {
+                           StageShared<K, P::NC, CHAR>& S, double& amax_x, double& amax_y, bool& bad) {
   constexpr int NC = P::NC;
   constexpr int NCF = ncoef2d(K);
   constexpr int MD = maxdeg(K);
   constexpr int NPLU = NC * 3;
   const int lane = threadIdx.x;
-  const int col = lane;
   const int i = i0 - 2 + lane;
   const int rend = min(j0 + H, in.ny);          // exclusive end of output rows
   const bool out_lane = lane >= 2 && lane <= LANES - 3 && i < in.nx;
-  const double idx_ = 1.0 / in.dx, idy = 1.0 / in.dy;
-  const double i2dx = 0.5 * idx_, i2dy = 0.5 * idy;
   const double ax = in.alpha_in[0], ay = in.alpha_in[1];
   const double dt = *in.dt;
   const double tb = DMR ? *in.t_end - in.t_ofs * dt : 0.0;   // boundary time of this stage
+  const double rxy = uniform(in.dy / in.dx);
+  const double cdt = uniform(0.5 * dt / in.dy);
   const bool use_u0 = A.ca != 0.0;
   const double* __restrict__ Us = A.Us + in.offset;
   const double* __restrict__ U0 = A.U0 + in.offset;
@@ -287,51 +343,224 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
   // moment planes of the output, as an element offset from Uout (0: Uout's own)
   const long long mom_off = A.Uout_mom ? elem_offset(A.Uout, A.Uout_mom) : 0;
 
-  double reg[NPLU];
-#pragma unroll 1
-  for (int r = j0 - 2; r <= j0; ++r) {
+  Window<NPLU>& W = S.W;
+  constexpr bool RICH = rich_lds<K, NC, CHAR>();
+  const bool wide = rows_aligned(Us, in, i0), wide0 = rows_aligned(U0, in, i0);
+  // rows of the double Mach reflection that hold ghost cells are built in registers
+  auto plain_row = [&](int r) { return !DMR || (r >= 0 && r < in.ny && i0 >= 2 && i0 + LANES - 2 <= in.nx); };
+  auto built_row = [&](int r) {
+    double reg[NPLU];
     fetch_row<NPLU, DMR>(Us, in, i0, r, lane, reg, tb);
     store_row<NPLU>(W, slot_of(r), lane, reg);
+  };
+#pragma unroll 1
+  for (int r = j0 - 2; r <= j0; ++r) {
+    if (plain_row(r))
+      dma_row<NPLU>(Us, in, in.plane, i0, ghost(r, in.ny, in.bcy), lane, &W.at(slot_of(r), 0, 0), wide);
+    else
+      built_row(r);
   }
-  __syncthreads();
 
-  constexpr bool CL = carry_in_lds<K, NC>();
-  double topR[CL ? 1 : NC][4];    // top trace of the row below (face j-1/2 of the current row)
-  double partR[CL ? 1 : NC][3];   // residual of the row below without its top face
-  auto prevTop = [&](int c, int q) -> double& {
-    if constexpr (CL) return T.top[c * 4 + q][col];
-    else return topR[c][q];
-  };
-  auto part = [&](int c, int m) -> double& {
-    if constexpr (CL) return T.part[c * 3 + m][col];
-    else return partR[c][m];
-  };
+  // carried from row to row: the share of the row below in the face between the
+  // two (T: mean and moment), and that row's residual without its top face (Y)
+  double T[2][NC], Y[NC][3];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) prevTop(c, q) = 0.0;
-#pragma unroll
-    for (int m = 0; m < 3; ++m) part(c, m) = 0.0;
+    T[0][c] = T[1][c] = Y[c][0] = Y[c][1] = Y[c][2] = 0.0;
+    if constexpr (RICH) {
+      S.cy.t[c][lane] = make_double2(0.0, 0.0);
+      S.cy.y[c][lane] = make_double2(0.0, 0.0);
+      if (c < 2) S.cy.y[4 + c][lane] = make_double2(0.0, 0.0);
+    }
   }
+  dma_wait();
+
+  int sl = slot_of(j0 - 2), sm = slot_of(j0 - 1), sh = slot_of(j0);   // slots of the rows r - 1, r, r + 1
+  double avg[NC] = {};          // averages that this iteration (or the last) finished
+
+  auto speeds = [&](bool on) {
+    bool b = false;
+    const double vx = here(phys.speed(0, avg, b)), vy = here(phys.speed(1, avg, b));
+    amax_x = on ? fmax(amax_x, vx) : amax_x;
+    amax_y = on ? fmax(amax_y, vy) : amax_y;
+    bad |= on && b;
+  };
+
+  // the rest of a row, from its reconstruction cf on
+  auto finish_row = [&](const double (&cf)[NC][NCF], int r, int tested) __attribute__((always_inline)) {
+    const bool fin = r - 1 >= j0;   // this iteration finishes row r-1
+    const bool ring_lo = (r == j0 - 1), ring_hi = (r == rend);
+    // opaque in every iteration, so that no row of plane offsets is kept (and spilled)
+    // across the loop: walking from plane to plane costs two scalar additions
+    size_t plane = in.plane;
+    asm volatile("" : "+s"(plane));
+
+    // bottom face (i, r-1/2): this row's share completes it
+    double Gb[NC], Gt[NC];
+    yface_sums<K, NCF>(phys, cf, -1.0, -ay, Gb, Gt);
+    FAM_SCHED_FENCE();
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if constexpr (RICH) {
+        const double2 t = S.cy.t[c][lane], y = S.cy.y[c][lane], z = S.cy.y[4 + c / 2][lane];
+        T[0][c] = t.x;
+        T[1][c] = t.y;
+        Y[c][0] = y.x;
+        Y[c][1] = y.y;
+        Y[c][2] = c % 2 == 0 ? z.x : z.y;
+      }
+      Gb[c] += T[0][c];
+      Gt[c] += T[1][c];
+    }
+
+    // finish the row below: its top face is this row's bottom face.  All lanes
+    // compute (those without output on the strip's first column); only the stores
+    // are masked, so that no register is moved or spilled under a partial mask.
+    if (fin) {
+      const ptrdiff_t idx = (ptrdiff_t)(r - 1) * in.nx + (i0 - 2);   // lane 0's column
+      const double* q0 = U0 + idx;
+      double* q = Uo + idx;
+      const int ul = out_lane ? lane : 2;
+      // at k = 5 two components at a time: their values of the step's start are read
+      // together, and no more are in flight than the registers hold (more, and the
+      // compiler waits for each to spill it)
+      constexpr int CB = K == 5 && NC == 4 && !RICH ? 2 : NC;
+#pragma unroll
+      for (int cb = 0; cb < NC; cb += CB) {
+        double v[CB * 3];
+        if (use_u0) {
+#pragma unroll
+          for (int p = 0; p < CB * 3; ++p) {
+            if constexpr (RICH) v[p] = S.u0.v[(cb * 3 + p) * LANES + lane];
+            else v[p] = q0[ul];
+            q0 += plane;
+          }
+        }
+#pragma unroll
+        for (int c = cb; c < cb + CB; ++c) {
+          const double D[3] = {Y[c][0] - Gb[c], Y[c][1] - Gt[c], fma(-0.5, Gb[c], Y[c][2])};
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            const double L = fma(cdt, D[m], W.at(sl, c * 3 + m, lane));
+            double& x = v[(c - cb) * 3 + m];
+            x = use_u0 ? fma(A.ca, x - L, L) : L;
+          }
+          avg[c] = v[(c - cb) * 3];
+        }
+        FAM_SCHED_FENCE();
+        if (out_lane) {
+#pragma unroll
+          for (int p = 0; p < CB * 3; ++p) {
+            (p % 3 == 0 ? q : q + mom_off)[lane] = v[p];
+            q += plane;
+          }
+        }
+        FAM_SCHED_FENCE();
+      }
+      if constexpr (!RICH) speeds(out_lane);
+    }
+    if (ring_hi) return;
+    // row r + 2 replaces row r - 1, which nothing reads any more
+    const bool pre = r + 2 <= rend + 1, dma = plain_row(r + 2);
+    dma_reads_done();
+    int dl = lane;
+    if constexpr (!RICH) asm volatile("" : "+v"(dl));   // its per-lane addresses are not kept between rows
+    if (pre && dma) dma_row<NPLU>(Us, in, plane, i0, ghost(r + 2, in.ny, in.bcy), dl, &W.at(sl, 0, 0), wide);
+    if constexpr (RICH) {
+      if (use_u0 && !ring_lo) dma_row<NPLU>(U0, in, plane, i0, r, lane, S.u0.v, wide0);
+    }
+    FAM_SCHED_FENCE();
+
+    if (!ring_lo) {
+      // the four interior lines y = eta_q: on each, the x-face points (both
+      // sides' shares) and four volume points
+      double Fb[NC], Ft[NC];     // left face: mean and moment along it
+      typename P::Volume V{};
+#pragma unroll
+      for (int c = 0; c < NC; ++c) Fb[c] = Ft[c] = 0.0;
+      // the wave speeds of the row just finished: a long chain of dependent
+      // operations, which a lone wave fills with the first line's independent ones
+      // (for all lanes, so that no branch keeps them apart)
+      if constexpr (RICH) speeds(fin && out_lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double up[3][NC], um[3][NC];   // values at xi = +-GS0, +-GS1, +-1/2
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          double Q[MD + 1];
+          line_y<K>(cf[c], qnode(q), qsign(q), Q);
+#pragma unroll
+          for (int n = 0; n < 3; ++n) pair_x<MD>(Q, n, up[n][c], um[n][c]);
+        }
+        // the left face takes the left neighbour's right share
+        double gr[NC], gl[NC];
+        phys.face(0, up[2], ax, gr);
+        phys.face(0, um[2], -ax, gl);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const double F = from_left(gr[c]) + gl[c];
+          Fb[c] = fma(qw(q), F, Fb[c]);
+          Ft[c] = fma(qw(q) * qx(q), F, Ft[c]);
+        }
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const double w = (n == 0 ? GW0 : GW1) * qw(q);
+          phys.volume(up[n], w, V);
+          phys.volume(um[n], w, V);
+        }
+        FAM_SCHED_FENCE();
+      }
+      // the right face is the right neighbour's left face
+      double Lb[NC], Rb[NC], Lt[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const double FbR = from_right(Fb[c]), FtR = from_right(Ft[c]);
+        Lb[c] = FbR - Fb[c];
+        Rb[c] = FbR + Fb[c];
+        Lt[c] = FtR - Ft[c];
+      }
+      double V1[NC], V2[NC];
+      {
+        double mean[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) mean[c] = cf[c][0];
+        phys.volume_sums(mean, V, V1, V2);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        Y[c][0] = fma(-rxy, Lb[c], Gb[c]);
+        Y[c][1] = fma(rxy, fma(-0.5, Rb[c], 2.0 * V1[c]), Gt[c]);
+        Y[c][2] = fma(-rxy, Lt[c], fma(-0.5, Gb[c], 2.0 * V2[c]));
+      }
+    }
+    FAM_SCHED_FENCE();
+    // this row's share of its top face
+    yface_sums<K, NCF>(phys, cf, 1.0, ay, T[0], T[1]);
+    if constexpr (RICH) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        S.cy.t[c][lane] = make_double2(T[0][c], T[1][c]);
+        if (!ring_lo) {
+          S.cy.y[c][lane] = make_double2(Y[c][0], Y[c][1]);
+          if (c % 2 == 0) S.cy.y[4 + c / 2][lane] = make_double2(Y[c][2], Y[c + 1][2]);
+        }
+      }
+    }
+
+    if constexpr (DMR) {
+      if (pre && !dma) built_row(r + 2);
+    }
+    dma_wait();
+    if constexpr (PP) {
+      // the iteration reconstructs (and limits) row r: its cost in plain rows, for
+      // the next launch's partition (rows of this segment only)
+      if (A.row_cost && lane == 0 && r >= j0 && r < rend)
+        A.row_cost[(size_t)(i0 / STRIP) * in.ny + r] = tested > 0 ? ROW_TEST + ROW_CELL * tested : 1.0f;
+    }
+  };
 
 #pragma unroll 1
   for (int r = j0 - 1; r <= rend; ++r) {
-    long long t_row = 0;
-    if constexpr (PP) {
-      if (A.row_cost) t_row = clock64();
-    }
-    const bool pre = (r + 2 <= rend + 1);
-    if (pre) fetch_row<NPLU, DMR>(Us, in, i0, r + 2, lane, reg, tb);
-    const bool fin = (r - 1 >= j0) && out_lane;   // this iteration finishes row r-1
-    double u0row[NPLU];
-    if (fin && use_u0) {
-      const size_t idx = (size_t)(r - 1) * in.nx + i;
-#pragma unroll
-      for (int p = 0; p < NPLU; ++p) u0row[p] = U0[p * in.plane + idx];
-    }
-    const int sl = slot_of(r - 1), sm = slot_of(r), sh = slot_of(r + 1);
-    const bool ring_lo = (r == j0 - 1), ring_hi = (r == rend);
-
     // reconstruction of all components
     double cf[NC][NCF];
     if constexpr (CHAR) {
@@ -341,7 +570,7 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
       {
         double a[NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) a[c] = W.v[sm][c * 3][col];
+        for (int c = 0; c < NC; ++c) a[c] = W.at(sm, c * 3, lane);
         char_basis_x<2>(phys.g, a, La, Ra);
       }
 #pragma unroll
@@ -352,7 +581,7 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           double g0[9], g1[9], g2[9];
-          gather<K>(W, c, col, sl, sm, sh, g0, g1, g2);
+          gather<K>(W, c, lane, sl, sm, sh, g0, g1, g2);
 #pragma unroll
           for (int l = 0; l < 9; ++l) {
             u0[l] = fma(La[w][c], g0[l], u0[l]);
@@ -379,166 +608,64 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
         }
       }
     } else {
+      // a lone wave reads the next component's stencil while it works on this one's
+      double u0[2][9], u1[2][9], u2[2][9];
+      if constexpr (RICH) gather<K>(W, 0, lane, sl, sm, sh, u0[0], u1[0], u2[0]);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        double u0[9], u1[9], u2[9];
-        gather<K>(W, c, col, sl, sm, sh, u0, u1, u2);
+        if constexpr (!RICH) gather<K>(W, c, lane, sl, sm, sh, u0[c & 1], u1[c & 1], u2[c & 1]);
+        else if (c + 1 < NC) gather<K>(W, c + 1, lane, sl, sm, sh, u0[(c + 1) & 1], u1[(c + 1) & 1], u2[(c + 1) & 1]);
+        FAM_SCHED_FENCE();
         double tmp[23];
-        coeffs2d<K>(u0, u1, u2, tmp, false);
+        coeffs2d<K>(u0[c & 1], u1[c & 1], u2[c & 1], tmp, false);
 #pragma unroll
         for (int l = 0; l < NCF; ++l) cf[c][l] = tmp[l];
+        FAM_SCHED_FENCE();
       }
     }
 
-    // optional positivity limiter on this cell's reconstruction
-    if constexpr (PP) pp_limiter<K, NCF, MD>(phys, cf, bad, lane, PS);
-
-    // bottom trace -> y-face flux below the current row: (i, r-1/2)
-    double Gb[NC], Gt[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) Gb[c] = Gt[c] = 0.0;
-    {
-      double bt[NC][4];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        double E[MD + 1][4], O[MD + 1][3];
-        contract_y<NCF, MD>(cf[c], E, O);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bt[c][q] = eval_pt<MD>(E, O, qnode(q), qsign(q), 2, -1.0);
-      }
-      if (!ring_lo) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          double ul[NC], ur[NC], fl[NC], fr[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) { ul[c] = prevTop(c, q); ur[c] = bt[c][q]; }
-          phys.flux(1, ul, fl);
-          phys.flux(1, ur, fr);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const double fh = 0.5 * (fl[c] + fr[c]) - 0.5 * ay * (ur[c] - ul[c]);
-            Gb[c] = fma(qw(q), fh, Gb[c]);
-            Gt[c] = fma(qw(q) * qx(q), fh, Gt[c]);
-          }
-        }
-      }
-    }
-
-    // finish the row below: its top face is this row's bottom face
-    if (fin) {
-      const size_t idx = (size_t)(r - 1) * in.nx + i;
-      double avg[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double Rm[3] = {part(c, 0) - Gb[c] * idy, part(c, 1) - Gt[c] * idy, part(c, 2) - Gb[c] * i2dy};
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          const double L = W.v[sl][c * 3 + m][col] + dt * Rm[m];
-          const double v = use_u0 ? fma(A.ca, u0row[c * 3 + m] - L, L) : L;
-          Uo[(c * 3 + m) * in.plane + idx + (m == 0 ? 0 : mom_off)] = v;
-          if (m == 0) avg[c] = v;
-        }
-      }
-      amax_x = fmax(amax_x, phys.speed(0, avg, bad));
-      amax_y = fmax(amax_y, phys.speed(1, avg, bad));
-    }
-    if (ring_hi) break;
-
-    // top trace of this row (bottom state of the next y-face)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      double E[MD + 1][4], O[MD + 1][3];
-      contract_y<NCF, MD>(cf[c], E, O);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) prevTop(c, q) = eval_pt<MD>(E, O, qnode(q), qsign(q), 2, 1.0);
-    }
-
-    if (!ring_lo) {
-      // x-face left of this lane: (i-1/2, r); left state = right trace of lane-1
-      double Fb[NC], Ft[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) Fb[c] = Ft[c] = 0.0;
-      {
-        double rt[NC][4], lt[NC][4];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          double E[MD + 1][4], O[MD + 1][3];
-          contract_y<NCF, MD>(cf[c], E, O);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            rt[c][q] = eval_pt<MD>(E, O, 2, 1.0, qnode(q), qsign(q));
-            lt[c][q] = eval_pt<MD>(E, O, 2, -1.0, qnode(q), qsign(q));
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          double ul[NC], ur[NC], fl[NC], fr[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            ul[c] = from_left(rt[c][q]);
-            ur[c] = lt[c][q];
-          }
-          phys.flux(0, ul, fl);
-          phys.flux(0, ur, fr);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const double fh = 0.5 * (fl[c] + fr[c]) - 0.5 * ax * (ur[c] - ul[c]);
-            Fb[c] = fma(qw(q), fh, Fb[c]);
-            Ft[c] = fma(qw(q) * qx(q), fh, Ft[c]);
-          }
-        }
-      }
-      double FbR[NC], FtR[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        FbR[c] = from_right(Fb[c]);
-        FtR[c] = from_right(Ft[c]);
-      }
-      // volume terms: 4x4 Gauss points
-      double V1[NC], V2[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) V1[c] = V2[c] = 0.0;
-#pragma unroll
-      for (int qy = 0; qy < 4; ++qy) {
-        double vals[4][NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          double E[MD + 1][4], O[MD + 1][3];
-          contract_y<NCF, MD>(cf[c], E, O);
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq) vals[qq][c] = eval_pt<MD>(E, O, qnode(qq), qsign(qq), qnode(qy), qsign(qy));
-        }
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          double f1[NC], f2[NC];
-          phys.flux2(vals[qq], f1, f2);
-          const double w = qw(qq) * qw(qy);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            V1[c] = fma(w, f1[c], V1[c]);
-            V2[c] = fma(w, f2[c], V2[c]);
-          }
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        part(c, 0) = -(FbR[c] - Fb[c]) * idx_ + Gb[c] * idy;
-        part(c, 1) = V1[c] * idx_ - (FbR[c] + Fb[c]) * i2dx + Gt[c] * idy;
-        part(c, 2) = V2[c] * idy - Gb[c] * i2dy - (FtR[c] - Ft[c]) * idx_;
-      }
-    }
-
-    // rotate the window: row r+2 replaces row r-1
-    __syncthreads();
-    if (pre) store_row<NPLU>(W, slot_of(r + 2), lane, reg);
-    __syncthreads();
     if constexpr (PP) {
-      // the iteration reconstructs (and limits) row r: its cost, for the next
-      // launch's partition (rows of this segment only)
-      if (A.row_cost && lane == 0 && r >= j0 && r < rend)
-        A.row_cost[(size_t)(i0 / STRIP) * in.ny + r] = (float)(clock64() - t_row);
+      // rare: 0.45 % of the cells, in 4.5 % of the rows of the four-quadrant problem
+      double eps = 0.0;
+      const unsigned long long todo = pp_cheap_test<K, NCF>(phys, cf, bad, lane, eps);
+      if (__builtin_expect(todo != 0, 0)) {
+        if constexpr (!RICH && K == 5) {
+          // what the row carries waits in scratch memory meanwhile: kept in registers,
+          // it or some coefficients would be spilled in every row
+          double park[5 * NC];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            park[5 * c] = T[0][c];
+            park[5 * c + 1] = T[1][c];
+#pragma unroll
+            for (int m = 0; m < 3; ++m) park[5 * c + 2 + m] = Y[c][m];
+          }
+          asm volatile("" : : "v"((ScratchDouble*)park) : "memory");   // keeps it there
+          pp_exact<K, NCF, MD>(phys, cf, todo, eps, lane, S.nwork);
+          asm volatile("" : : "v"((ScratchDouble*)park) : "memory");
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            T[0][c] = park[5 * c];
+            T[1][c] = park[5 * c + 1];
+#pragma unroll
+            for (int m = 0; m < 3; ++m) Y[c][m] = park[5 * c + 2 + m];
+          }
+        } else {
+          pp_exact<K, NCF, MD>(phys, cf, todo, eps, lane, S.nwork);
+        }
+      }
+      finish_row(cf, r, __popcll(todo));
+    } else {
+      finish_row(cf, r, 0);
+    }
+    {
+      const int t = sl;
+      sl = sm;
+      sm = sh;
+      sh = t;
     }
   }
+  if constexpr (RICH) speeds(out_lane && rend > j0);   // the last row's
   __syncthreads();
 }
 
@@ -547,8 +674,8 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
 // and p(0, +-1/2), are fixed linear functionals of its 3x3 stencil moments
 // (weights in fam_eval.h, folded at compile time).
 // ---------------------------------------------------------------------------
-template <int K, bool FULL>
-__device__ __forceinline__ void centre_values(const Window& W, int c, int col, int sl, int sm, int sh,
+template <int K, bool FULL, int NC>
+__device__ __forceinline__ void centre_values(const Window<3 * NC>& W, int c, int col, int sl, int sm, int sh,
                                               double (&out)[4]) {
   double u0[9], u1[9], u2[9];
   gather<K>(W, c, col, sl, sm, sh, u0, u1, u2);
@@ -568,7 +695,7 @@ __device__ __forceinline__ void centre_values(const Window& W, int c, int col, i
 
 template <int K, class P, bool FULL, bool DMR = false>
 __device__ void oe_tile(const P& phys, const OEArgs& A, const Inst& in, int i0, int j0, int H,
-                        Window& W, double (&t1s)[8], bool& bad) {
+                        Window<3 * P::NC>& W, double (&t1s)[8], bool& bad) {
   constexpr int NC = P::NC;
   constexpr int NPLU = NC * 3;
   const int lane = threadIdx.x;
@@ -618,7 +745,7 @@ __device__ void oe_tile(const P& phys, const OEArgs& A, const Inst& in, int i0, 
   for (int q = 0; q < 2; ++q) {
     double a1[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) a1[c] = W.v[slot_of(j0 - 2 + q)][c * 3][col];
+    for (int c = 0; c < NC; ++c) a1[c] = W.at(slot_of(j0 - 2 + q), c * 3, col);
     spx[q] = phys.speed(0, a1, bad);
     spy[q] = phys.speed(1, a1, bad);
   }
@@ -639,7 +766,7 @@ __device__ void oe_tile(const P& phys, const OEArgs& A, const Inst& in, int i0, 
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       double ctr[4];
-      centre_values<K, FULL>(W, c, col, sl, sm, sh, ctr);
+      centre_values<K, FULL, NC>(W, c, col, sl, sm, sh, ctr);
       const double Jb = fabs(ctr[3] - prevTopC[c]);
       {
         const double Jy = prevJb[c] + Jb;
@@ -660,7 +787,7 @@ __device__ void oe_tile(const P& phys, const OEArgs& A, const Inst& in, int i0, 
             // S = sum, M = max, m = min of the 3x3 averages (column-wise, then
             // across the neighbouring lanes); max |v - S| = max(M - S, S - m) and
             // max |v| = max(|M|, |m|) (rounding is monotone)
-            const double v0 = W.v[sl][c * 3][col], v1 = W.v[sm][c * 3][col], v2 = W.v[sh][c * 3][col];
+            const double v0 = W.at(sl, c * 3, col), v1 = W.at(sm, c * 3, col), v2 = W.at(sh, c * 3, col);
             const double cs = v0 + v1 + v2;
             const double cM = fmax(fmax(v0, v1), v2), cmn = fmin(fmin(v0, v1), v2);
             const double S = from_left(cs) + cs + from_right(cs);
@@ -684,9 +811,9 @@ __device__ void oe_tile(const P& phys, const OEArgs& A, const Inst& in, int i0, 
       if (A.delta_out) A.delta_out[idx] = delta;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        if (write_avg) Uo[(c * 3 + 0) * in.plane + idx] = W.v[sl][c * 3 + 0][col];
-        Uo[(c * 3 + 1) * in.plane + idx] = W.v[sl][c * 3 + 1][col] * delta;
-        Uo[(c * 3 + 2) * in.plane + idx] = W.v[sl][c * 3 + 2][col] * delta;
+        if (write_avg) Uo[(c * 3 + 0) * in.plane + idx] = W.at(sl, c * 3 + 0, col);
+        Uo[(c * 3 + 1) * in.plane + idx] = W.at(sl, c * 3 + 1, col) * delta;
+        Uo[(c * 3 + 2) * in.plane + idx] = W.at(sl, c * 3 + 2, col) * delta;
       }
     }
     if (r == rend) break;
@@ -695,7 +822,7 @@ __device__ void oe_tile(const P& phys, const OEArgs& A, const Inst& in, int i0, 
     {
       double a1[NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) a1[c] = W.v[sh][c * 3][col];
+      for (int c = 0; c < NC; ++c) a1[c] = W.at(sh, c * 3, col);
       spx[2] = phys.speed(0, a1, bad);
       spy[2] = phys.speed(1, a1, bad);
     }
@@ -737,7 +864,7 @@ __device__ __forceinline__ Burgers make_phys<Burgers>(const PhysParams& pp) {
 }
 template <>
 __device__ __forceinline__ Euler<2> make_phys<Euler<2>>(const PhysParams& pp) {
-  return Euler<2>{pp.gamma};
+  return Euler<2>(pp.gamma);
 }
 
 __device__ __forceinline__ void flush_wave_results(double amax_x, double amax_y, bool bad,
@@ -772,10 +899,8 @@ __device__ __forceinline__ int heavy_first_slot(int L, int N, int nh) {
 }
 
 template <int K, class P, bool PP, bool DMR, bool CHAR = false>
-__global__ void FAM_STAGE_ATTR stage2d_kernel(StageArgs A, Inst in, int H) {
-  __shared__ Window W;
-  __shared__ PPStage<K> PS;
-  __shared__ StageCarry<carry_in_lds<K, P::NC>()> T;
+__global__ void FAM_STAGE_ATTR(K, CHAR) stage2d_kernel(StageArgs A, Inst in, int H) {
+  FAM_STAGE_SHARED(K, P::NC, CHAR);
   if (*A.done) return;
   const P phys = make_phys<P>(A.phys);
   double amx = 0.0, amy = 0.0;
@@ -787,23 +912,23 @@ __global__ void FAM_STAGE_ATTR stage2d_kernel(StageArgs A, Inst in, int H) {
     // tiles with limiter work first (spread over the XCDs in turn), then the
     // others in the XCD-aware order of their row-major index
     const int N = gridDim.x;
-    tile = A.tile_perm[heavy_first_slot(blockIdx.x, N, A.tile_perm[N])];
+    tile = __builtin_amdgcn_readfirstlane(A.tile_perm[heavy_first_slot(blockIdx.x, N, A.tile_perm[N])]);
     i0 = (tile % strips) * STRIP;
     j0 = (tile / strips) * H;
-    PS.nwork = 0;
+    S.nwork = 0;
   } else {
     const int T = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     i0 = (T % gridDim.x) * STRIP;
     j0 = (T / gridDim.x) * H;
   }
-  stage_tile<K, P, PP, DMR, CHAR>(phys, A, in, i0, j0, H, W, PS, T, amx, amy, bad);
+  stage_tile<K, P, PP, DMR, CHAR>(phys, A, in, i0, j0, H, S, amx, amy, bad);
   flush_wave_results(amx, amy, bad, in.alpha_out, A.flag);
   if constexpr (PP) {
-    if (threadIdx.x == 0) A.tile_work[tile] = PS.nwork;
+    if (threadIdx.x == 0) A.tile_work[tile] = S.nwork;
   }
 }
 
-constexpr int ORDER_MIN_TILES = 1024;   // 256 CUs x 4 SIMDs, one stage wave each
+constexpr int ORDER_MIN_TILES = 1024;   // 256 CUs x 4 SIMDs: one stage wave on each
 
 // tile_perm := tiles with tile_work > 0 first, then the others, each group in
 // index order (one block; each thread owns a contiguous chunk)
@@ -842,11 +967,9 @@ __global__ void tile_identity_kernel(int* __restrict__ perm, int* __restrict__ w
 }
 
 template <int K, class P, bool DMR, bool CHAR = false>
-__global__ void FAM_STAGE_ATTR stage2d_list_kernel(StageArgs A, Inst in, const int4* __restrict__ seg,
+__global__ void FAM_STAGE_ATTR(K, CHAR) stage2d_list_kernel(StageArgs A, Inst in, const int4* __restrict__ seg,
                                                     const int* __restrict__ nseg) {
-  __shared__ Window W;
-  __shared__ PPStage<K> PS;
-  __shared__ StageCarry<carry_in_lds<K, P::NC>()> T;
+  FAM_STAGE_SHARED(K, P::NC, CHAR);
   if (*A.done) return;
   const int n = *nseg;
   if ((int)blockIdx.x >= n) return;
@@ -856,8 +979,8 @@ __global__ void FAM_STAGE_ATTR stage2d_list_kernel(StageArgs A, Inst in, const i
   const P phys = make_phys<P>(A.phys);
   double amx = 0.0, amy = 0.0;
   bool bad = false;
-  PS.nwork = 0;
-  stage_tile<K, P, true, DMR, CHAR>(phys, A, in, it.y, it.z, it.w, W, PS, T, amx, amy, bad);
+  S.nwork = 0;
+  stage_tile<K, P, true, DMR, CHAR>(phys, A, in, it.y, it.z, it.w, S, amx, amy, bad);
   flush_wave_results(amx, amy, bad, in.alpha_out, A.flag);
 }
 
@@ -1027,11 +1150,9 @@ __global__ void fill_kernel(float* __restrict__ p, float v, size_t n) {
 }
 
 template <int K, class P, bool PP>
-__global__ void FAM_STAGE_ATTR stage2d_batched_kernel(StageArgs A, const Inst* __restrict__ insts,
+__global__ void FAM_STAGE_ATTR(K, false) stage2d_batched_kernel(StageArgs A, const Inst* __restrict__ insts,
                                                                 const int4* __restrict__ work, int nwork) {
-  __shared__ Window W;
-  __shared__ PPStage<K> PS;
-  __shared__ StageCarry<carry_in_lds<K, P::NC>()> T;
+  FAM_STAGE_SHARED(K, P::NC, false);
   const P phys = make_phys<P>(A.phys);
   bool bad = false;
   // one item per workgroup: the XCD-aware order (limiter on: heavy items first)
@@ -1042,15 +1163,16 @@ __global__ void FAM_STAGE_ATTR stage2d_batched_kernel(StageArgs A, const Inst* _
     int wi;
     if constexpr (PP) wi = A.tile_perm[one_each ? heavy_first_slot(w, nwork, A.tile_perm[nwork]) : w];
     else wi = one_each ? xcd_tile(w, nwork) : w;
+    wi = __builtin_amdgcn_readfirstlane(wi);   // in scalar registers, and with it the item and its instance
     const int4 it = work[wi];             // (instance, i0, j0, H)
     const Inst in = insts[it.x];
-    if (in.done && *in.done) continue;
+    if (in.done && __builtin_amdgcn_readfirstlane(*in.done)) continue;
     double amx = 0.0, amy = 0.0;
-    if constexpr (PP) PS.nwork = 0;
-    stage_tile<K, P, PP>(phys, A, in, it.y, it.z, it.w, W, PS, T, amx, amy, bad);
+    if constexpr (PP) S.nwork = 0;
+    stage_tile<K, P, PP>(phys, A, in, it.y, it.z, it.w, S, amx, amy, bad);
     flush_wave_results(amx, amy, false, in.alpha_out, A.flag);
     if constexpr (PP) {
-      if (threadIdx.x == 0) A.tile_work[wi] = PS.nwork;
+      if (threadIdx.x == 0) A.tile_work[wi] = S.nwork;
     }
   }
   if (__any(bad) && threadIdx.x == 0) atomicOr(A.flag, 1);
@@ -1058,7 +1180,7 @@ __global__ void FAM_STAGE_ATTR stage2d_batched_kernel(StageArgs A, const Inst* _
 
 template <int K, class P, bool DMR>
 __global__ void FAM_OE_ATTR oe2d_kernel(OEArgs A, Inst in, int H) {
-  __shared__ Window W;
+  __shared__ Window<3 * P::NC> W;
   __shared__ double t1s[8];
   if (*A.done) return;
   const P phys = make_phys<P>(A.phys);
@@ -1075,16 +1197,16 @@ __global__ void FAM_OE_ATTR oe2d_kernel(OEArgs A, Inst in, int H) {
 template <int K, class P>
 __global__ void FAM_OE_ATTR oe2d_batched_kernel(OEArgs A, const Inst* __restrict__ insts,
                                                              const int4* __restrict__ work, int nwork) {
-  __shared__ Window W;
+  __shared__ Window<3 * P::NC> W;
   __shared__ double t1s[8];
   const P phys = make_phys<P>(A.phys);
   bool bad = false;
   const bool one_each = (int)gridDim.x == nwork;   // then the XCD-aware order
 #pragma unroll 1
   for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-    const int4 it = work[one_each ? xcd_tile(w, nwork) : w];
+    const int4 it = work[__builtin_amdgcn_readfirstlane(one_each ? xcd_tile(w, nwork) : w)];
     const Inst in = insts[it.x];
-    if (in.done && *in.done) continue;
+    if (in.done && __builtin_amdgcn_readfirstlane(*in.done)) continue;
     if (K == 6 && A.k6_table)
       oe_tile<K, P, true>(phys, A, in, it.y, it.z, it.w, W, t1s, bad);
     else
@@ -1209,7 +1331,7 @@ static void launch_stage2d_d(const StageArgs& A, const Inst& in, int H, hipStrea
     hipLaunchKernelGGL((stage2d_kernel<K, P, true, DMR, CHAR>), dim3(ntiles), dim3(LANES), 0, s, A, in, H);
     // up to one tile per wave slot of the chip every tile starts at once: the
     // order stays the identity set with the tile height
-    if (ntiles > ORDER_MIN_TILES)
+    if (ntiles > ORDER_MIN_TILES * stage_waves(K, P::NC, CHAR))
       hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(1024), 0, s, A.tile_work, const_cast<int*>(A.tile_perm),
                          ntiles);
   } else {

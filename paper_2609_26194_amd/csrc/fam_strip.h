@@ -9,52 +9,56 @@
 namespace fam {
 
 constexpr int LANES = 64;
-constexpr int NPL = 12;            // planes held in LDS for up to 4 components x 3 moments
 
 // ---------------------------------------------------------------------------
 // LDS row window: lane l holds LDS column l = grid column i0 - 2 + l.  Lanes 0
 // and 63 only load; lanes 1 and 62 are ring columns; lanes 2..61 write output.
 // ---------------------------------------------------------------------------
-struct Window {
-  double v[3][NPL][LANES];
+template <int NPLU>
+struct alignas(16) Window {
+  // two values before and after the rows: the load-only lanes 0 and 63 read their
+  // missing neighbour column there or in the next plane, and nothing uses what
+  // they compute from it (two, not one, so that the rows start on 16 bytes)
+  double f[3 * NPLU * LANES + 4];
+  __device__ __forceinline__ double& at(int slot, int plane, int col) {
+    return f[2 + (slot * NPLU + plane) * LANES + col];
+  }
+  __device__ __forceinline__ double at(int slot, int plane, int col) const {
+    return f[2 + (slot * NPLU + plane) * LANES + col];
+  }
 };
 
 // three row slots used as a ring: row r+2 is fetched into the slot of row r-1
 // once every read of row r-1 in the current iteration is done
 __device__ __forceinline__ int slot_of(int r) { return ((r % 3) + 3) % 3; }
 
-// the double Mach reflection ghost cells of row r, column ci (at least one
-// outside the mesh) at boundary time tb; see fam_config.dmr
+// row r, column ci of the double Mach reflection at boundary time tb (mesh or ghost
+// cells; see fam_config.dmr), for all lanes at once
 template <int NPLU>
-__device__ __forceinline__ void dmr_ghost(const double* __restrict__ U, const Inst& in, int r, int ci, double tb,
+__device__ __forceinline__ void dmr_cells(const double* __restrict__ U, const Inst& in, int r, int ci, double tb,
                                           double (&reg)[NPLU], long long moff) {
   const double xc = in.x0 + (ci + 0.5) * in.dx;
-  int which = -1;   // 0: post-shock state, 1: pre-shock state, -1: copy or mirror
-  if (r >= in.ny)   // top: the exact shock line at the upper boundary
-    which = xc < 1.0 / 6.0 + (in.ytop + 20.0 * tb) * 0.57735026918962576451 ? 0 : 1;
-  else if (r < 0 ? xc < 1.0 / 6.0 : ci < 0)   // bottom inflow part, left inflow
-    which = 0;
-  if (which >= 0) {
-    // (rho, u, v, p) = (8, 8.25 cos 30deg, -8.25 sin 30deg, 116.5) behind the shock,
-    // (1.4, 0, 0, 1) ahead; conservative, with 1/(gamma - 1) = in.dmr_einv
-    constexpr double rl = 8.0, ul = 8.25 * 0.86602540378443864676, vl = -8.25 * 0.5, pl = 116.5;
-    const double post[4] = {rl, rl * ul, rl * vl, pl * in.dmr_einv + 0.5 * rl * (ul * ul + vl * vl)};
-    const double pre[4] = {1.4, 0.0, 0.0, in.dmr_einv};
-#pragma unroll
-    for (int p = 0; p < NPLU; ++p) reg[p] = p % 3 == 0 ? (which == 0 ? post[p / 3] : pre[p / 3]) : 0.0;
-    return;
-  }
-  // right outflow (copy of the last column) and, below the mesh, the reflecting
-  // wall: mirror image of row -1 - r with rho v and the y-moments of the other
-  // components negated
-  const int gi = ci >= in.nx ? in.nx - 1 : ci;
-  const int gj = r < 0 ? -1 - r : r;
+  // top: the exact shock line at the upper boundary; bottom inflow part, left inflow
+  const bool top = r >= in.ny;
+  const bool behind = xc < 1.0 / 6.0 + (in.ytop + 20.0 * tb) * 0.57735026918962576451;
+  const bool post = top ? behind : r < 0 ? xc < 1.0 / 6.0 : ci < 0;
+  // (rho, u, v, p) = (8, 8.25 cos 30deg, -8.25 sin 30deg, 116.5) behind the shock,
+  // (1.4, 0, 0, 1) ahead; conservative, with 1/(gamma - 1) = in.dmr_einv
+  constexpr double rl = 8.0, ul = 8.25 * 0.86602540378443864676, vl = -8.25 * 0.5, pl = 116.5;
+  const double qpost[4] = {rl, rl * ul, rl * vl, pl * in.dmr_einv + 0.5 * rl * (ul * ul + vl * vl)};
+  const double qpre[4] = {1.4, 0.0, 0.0, in.dmr_einv};
+  // the others: the mesh cell itself, right outflow (copy of the last column) and,
+  // below the mesh, the reflecting wall: mirror image of row -1 - r with rho v and
+  // the y-moments of the other components negated
+  const int gi = min(max(ci, 0), in.nx - 1);
+  const int gj = min(r < 0 ? -1 - r : r, in.ny - 1);
   const size_t base = (size_t)gj * in.nx + gi;
 #pragma unroll
   for (int p = 0; p < NPLU; ++p) {
     const double v = U[p * in.plane + base + (p % 3 == 0 ? 0 : moff)];
     const bool neg = r < 0 && ((p / 3 == 2) ? (p % 3 != 2) : (p % 3 == 2));
-    reg[p] = neg ? -v : v;
+    const double ahead = p % 3 == 0 ? qpre[p / 3] : 0.0, back = p % 3 == 0 ? qpost[p / 3] : 0.0;
+    reg[p] = post ? back : top ? ahead : neg ? -v : v;
   }
 }
 
@@ -74,8 +78,8 @@ __device__ __forceinline__ void fetch_row(const double* __restrict__ U, const In
                                           int lane, double (&reg)[NPLU], double tb, long long moff = 0) {
   const int ci = i0 - 2 + lane;
   if constexpr (DMR) {
-    if (r < 0 || r >= in.ny || ci < 0 || ci >= in.nx) {
-      dmr_ghost<NPLU>(U, in, r, ci, tb, reg, moff);
+    if (r < 0 || r >= in.ny || i0 < 2 || i0 + LANES - 2 > in.nx) {
+      dmr_cells<NPLU>(U, in, r, ci, tb, reg, moff);
       return;
     }
   }
@@ -86,29 +90,75 @@ __device__ __forceinline__ void fetch_row(const double* __restrict__ U, const In
   for (int p = 0; p < NPLU; ++p) reg[p] = U[p * in.plane + base + (p % 3 == 0 ? 0 : moff)];
 }
 
-template <int NPLU>
-__device__ __forceinline__ void store_row(Window& W, int slot, int lane, const double (&reg)[NPLU]) {
-#pragma unroll
-  for (int p = 0; p < NPLU; ++p) W.v[slot][p][lane] = reg[p];
+// Row gj of the state U, columns i0 - 2 .. i0 + 61 (ghost columns mapped), straight
+// into LDS at dst (NPLU planes of 64 values), past the vector registers, which are
+// what the stage kernel is short of.  Asynchronous: dma_wait() before its data is
+// read, dma_reads_done() before it may overwrite what was read.  A strip without
+// ghost columns whose rows all start on 16 bytes moves 16 bytes per lane, two planes
+// with one instruction (6 for the 12 planes of the Euler equations); the others take
+// 4 bytes per lane, which any width and column map allows (24 instructions).
+using GlobalWord = const __attribute__((address_space(1))) unsigned;
+using LdsWord = __attribute__((address_space(3))) unsigned;
+
+// Both waits are explicit.  The compiler's own tracking takes an instruction's LDS
+// target for the bytes of one lane and would let reads of other lanes' data pass.
+// (A wave waits for itself: a workgroup is one wave.)
+__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void dma_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// whether every row of every plane of U starts on 16 bytes in this strip
+__device__ __forceinline__ bool rows_aligned(const double* U, const Inst& in, int i0) {
+  return i0 >= 2 && i0 + LANES - 2 <= in.nx && (((uintptr_t)U | (uintptr_t)(8 * (size_t)in.nx)) & 15) == 0;
 }
 
-// stencil of component c around LDS column col (clamped for the load-only lanes)
-template <int K>
-__device__ __forceinline__ void gather(const Window& W, int c, int col, int sl, int sm, int sh,
+template <int NPLU>
+__device__ __forceinline__ void dma_row(const double* __restrict__ U, const Inst& in, size_t plane, int i0, int gj,
+                                        int lane, double* dst, bool aligned) {
+  LdsWord* l = (LdsWord*)dst;
+  if (aligned) {
+    const double* row = U + ((size_t)gj * in.nx + (i0 - 2)) + ((lane >> 5) * plane + 2 * (lane & 31));
+#pragma unroll
+    for (int p = 0; p < NPLU; p += 2) {
+      if (p + 1 < NPLU || lane < 32)
+        __builtin_amdgcn_global_load_lds((GlobalWord*)row, l + p * 2 * LANES, 16, 0, 0);
+      row += 2 * plane;
+    }
+  } else {
+    const double* row = U + (size_t)gj * in.nx;
+    const int c0 = i0 - 2 + (lane >> 1);
+    GlobalWord* g0 = (GlobalWord*)(row + ghost(c0, in.nx, in.bcx)) + (lane & 1);
+    GlobalWord* g1 = (GlobalWord*)(row + ghost(c0 + LANES / 2, in.nx, in.bcx)) + (lane & 1);
+#pragma unroll
+    for (int p = 0; p < NPLU; ++p) {
+      __builtin_amdgcn_global_load_lds(g0, l + p * 2 * LANES, 4, 0, 0);
+      __builtin_amdgcn_global_load_lds(g1, l + p * 2 * LANES + LANES, 4, 0, 0);
+      g0 += 2 * plane;
+      g1 += 2 * plane;
+    }
+  }
+}
+
+template <int NPLU>
+__device__ __forceinline__ void store_row(Window<NPLU>& W, int slot, int lane, const double (&reg)[NPLU]) {
+#pragma unroll
+  for (int p = 0; p < NPLU; ++p) W.at(slot, p, lane) = reg[p];
+}
+
+// stencil of component c around LDS column col
+template <int K, class WIN>
+__device__ __forceinline__ void gather(const WIN& W, int c, int col, int sl, int sm, int sh,
                                        double (&u0)[9], double (&u1)[9], double (&u2)[9]) {
   const int sr[3] = {sl, sm, sh};
-  const int cm = col > 0 ? col - 1 : 0, cp = col < LANES - 1 ? col + 1 : LANES - 1;
-  const int cc[3] = {cm, col, cp};
 #pragma unroll
   for (int b = 0; b < 3; ++b)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       const int l = b * 3 + a;
-      u0[l] = W.v[sr[b]][c * 3 + 0][cc[a]];
+      u0[l] = W.at(sr[b], c * 3 + 0, col + a - 1);
       const bool x_used = (K >= 5) ? (l != 1 && l != 7) : (l == 4);
       const bool y_used = (K >= 5) ? (l != 3 && l != 5) : (l == 4);
-      u1[l] = x_used ? W.v[sr[b]][c * 3 + 1][cc[a]] : 0.0;
-      u2[l] = y_used ? W.v[sr[b]][c * 3 + 2][cc[a]] : 0.0;
+      u1[l] = x_used ? W.at(sr[b], c * 3 + 1, col + a - 1) : 0.0;
+      u2[l] = y_used ? W.at(sr[b], c * 3 + 2, col + a - 1) : 0.0;
     }
 }
 
