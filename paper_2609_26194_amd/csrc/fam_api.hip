@@ -98,11 +98,12 @@ static Inst make_inst(const fam_ctx* c, int i) {
 Inst inst_for(const fam_ctx* c, int i, int parity, int stage) {
   Inst in = make_inst(c, i);
   StepState* s = c->st + i;
+  auto set = [&](int p, int q) { return c->alpha + (size_t)i * fam::ALPHA_INST + (3 * p + q) * fam::ALPHA_SET; };
   if (stage < 3) {
-    in.alpha_in = &s->alpha[parity][stage][0];
-    in.alpha_out = stage < 2 ? &s->alpha[parity][stage + 1][0] : &s->alpha[1 - parity][0][0];
+    in.alpha_in = set(parity, stage);
+    in.alpha_out = stage < 2 ? set(parity, stage + 1) : set(1 - parity, 0);
   } else {
-    in.alpha_in = &s->alpha[parity][0][0];
+    in.alpha_in = set(parity, 0);
     in.alpha_out = nullptr;
   }
   in.dt = &s->dt;
@@ -127,6 +128,7 @@ static fam_status alloc_common(fam_ctx* c) {
   if (hipMalloc(&c->W1, bytes) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->W2, bytes) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->st, sizeof(StepState) * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
+  if (hipMalloc(&c->alpha, sizeof(double) * fam::ALPHA_INST * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->flag, sizeof(int) * 4) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->stats, sizeof(double) * 8 * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->partial, sizeof(double) * 4 * c->t1_blocks) != hipSuccess) return FAM_ERR_NOMEM;
@@ -143,6 +145,7 @@ static fam_status init_steps(fam_ctx* c) {
     StepState& s = h[i];
     std::memset(&s, 0, sizeof(s));
     const fam_config& f = c->cfg[i];
+    s.alpha = c->alpha + (size_t)i * fam::ALPHA_INST;
     s.cfl = f.cfl;
     const double e = f.dt_rule == 1 ? f.k / 3.0 : 1.0;
     s.hx = std::pow((f.x1 - f.x0) / f.nx, e);
@@ -150,6 +153,9 @@ static fam_status init_steps(fam_ctx* c) {
     s.dim = c->dim;
   }
   HIP_TRY(hipMemcpy(c->st, h.data(), sizeof(StepState) * c->ninst, hipMemcpyHostToDevice));
+  // the wave-speed slots start at zero, as after a reset
+  const std::vector<double> none((size_t)fam::ALPHA_INST * c->ninst, 0.0);
+  HIP_TRY(hipMemcpy(c->alpha, none.data(), sizeof(double) * none.size(), hipMemcpyHostToDevice));
   return FAM_OK;
 }
 
@@ -209,7 +215,7 @@ extern "C" void fam_destroy(fam_ctx* c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   destroy_graphs(c);
   fam_adjoint_free(c);
-  void* bufs[] = {c->W1,        c->W2,        c->st,       c->flag, c->stats,    c->partial,  c->dmax,
+  void* bufs[] = {c->W1,        c->W2,        c->st,       c->alpha, c->flag, c->stats,    c->partial,  c->dmax,
                   c->d_work,    c->tile_perm, c->tile_work, c->seg,  c->nseg,     c->row_cost, c->row_pref,
                   c->part_state};
   for (void* p : bufs)
@@ -376,10 +382,9 @@ extern "C" int fam_num_instances(const fam_ctx* c) { return c ? c->ninst : 0; }
 // enqueue helpers
 // ---------------------------------------------------------------------------
 void enqueue_alpha_full(fam_ctx* c, const double* U, int parity) {
-  fam::launch_zero_alpha(c->st, c->ninst, parity, c->stream);
   if (c->dim == 1) {
     Inst in = inst_for(c, 0, parity, 0);
-    in.alpha_out = &c->st[0].alpha[parity][0][0];
+    in.alpha_out = const_cast<double*>(in.alpha_in);
     fam::launch_alpha1d(c->sys, c->phys, U, in, c->flag, c->stream);
     return;
   }

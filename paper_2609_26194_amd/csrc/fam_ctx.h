@@ -24,6 +24,7 @@ struct fam_ctx {
   double* W1 = nullptr;
   double* W2 = nullptr;
   fam::StepState* st = nullptr;
+  double* alpha = nullptr;     // wave-speed slots, ALPHA_INST per instance
   int* flag = nullptr;
   double* stats = nullptr;     // Type I: [inst*8 + ...]
   double* partial = nullptr;   // Type I partial sums
@@ -79,6 +80,7 @@ fam::Inst inst_for(const fam_ctx* c, int i, int parity, int stage);
 fam_status reset_steps(fam_ctx* c, double t_final, double dt_fixed);
 fam_status save_clock(fam_ctx* c, std::vector<double>* t);
 fam_status restore_clock(fam_ctx* c, const std::vector<double>& t);
+// wave speeds of U into the stage-0 input slots, which reset_steps has cleared
 void enqueue_alpha_full(fam_ctx* c, const double* U, int parity);
 // Uout_mom: moment planes of the output (NULL: Uout's own)
 void enqueue_stage(fam_ctx* c, int s, int parity, const double* U0, const double* Us, double* Uout,

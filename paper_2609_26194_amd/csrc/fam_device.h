@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fam_kernels.h"
+
 namespace fam {
 
 // XCD-aware tile order.  The hardware hands consecutive workgroups to the chip's
@@ -300,10 +302,37 @@ struct Euler {
 // ---------------------------------------------------------------------------
 // reductions
 // ---------------------------------------------------------------------------
+// v of the lane that a DPP control pairs with this one within its row of 16
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp64(unsigned long long v) {
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)v, CTRL, 0xf, 0xf, false);
+  const unsigned hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), CTRL, 0xf, 0xf, false);
+  return (unsigned long long)hi << 32 | lo;
+}
+// v of a fixed lane, in scalar registers
+__device__ __forceinline__ unsigned long long lane64(unsigned long long v, int lane) {
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+  return (unsigned long long)hi << 32 | lo;
+}
+// op over the rows of 16 lanes (every lane holds its row's result): lanes 1 and 2
+// apart by quad permutes, then the mirrored half row and the mirrored row
+template <class F>
+__device__ __forceinline__ unsigned long long row_reduce(unsigned long long v, F op) {
+  v = op(v, dpp64<0xB1>(v));    // quad_perm [1,0,3,2]
+  v = op(v, dpp64<0x4E>(v));    // quad_perm [2,3,0,1]
+  v = op(v, dpp64<0x141>(v));   // row_half_mirror
+  return op(v, dpp64<0x140>(v));   // row_mirror
+}
+
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
+  auto op = [](unsigned long long a, unsigned long long b) {
+    return (unsigned long long)__double_as_longlong(
+        fmax(__longlong_as_double((long long)a), __longlong_as_double((long long)b)));
+  };
+  const unsigned long long r = row_reduce((unsigned long long)__double_as_longlong(v), op);
+  return __longlong_as_double(
+      (long long)op(op(lane64(r, 0), lane64(r, 16)), op(lane64(r, 32), lane64(r, 48))));
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -315,6 +344,24 @@ __device__ __forceinline__ double wave_sum(double v) {
 // max of non-negative doubles through their bit patterns (order-preserving)
 __device__ __forceinline__ void atomic_max_nonneg(double* addr, double v) {
   atomicMax(reinterpret_cast<unsigned long long*>(addr), (unsigned long long)__double_as_longlong(v));
+}
+
+// The wave speeds of a state: the largest of its slots (as bit patterns, like the
+// atomics), one slot per lane, lanes 32 to 63 the same again.
+__device__ __forceinline__ double2 alpha_load(const double* __restrict__ set) {
+  return *reinterpret_cast<const double2*>(set + (threadIdx.x & (ALPHA_SLOTS - 1)) * ALPHA_STRIDE);
+}
+__device__ __forceinline__ void alpha_max(double2 a, double& ax, double& ay) {
+  static_assert(ALPHA_SLOTS == 32, "two rows of 16 lanes");
+  auto op = [](unsigned long long p, unsigned long long q) { return p > q ? p : q; };
+  const unsigned long long x = row_reduce((unsigned long long)__double_as_longlong(a.x), op);
+  const unsigned long long y = row_reduce((unsigned long long)__double_as_longlong(a.y), op);
+  ax = __longlong_as_double((long long)op(lane64(x, 0), lane64(x, 16)));
+  ay = __longlong_as_double((long long)op(lane64(y, 0), lane64(y, 16)));
+}
+// a wave's slot: one lane adds the wave's maxima
+__device__ __forceinline__ double* alpha_slot(double* set, unsigned wave) {
+  return set + (wave & (ALPHA_SLOTS - 1)) * ALPHA_STRIDE;
 }
 
 // ghost-cell index map: periodic wrap or transmissive clamp

@@ -28,8 +28,8 @@ struct Inst {
   size_t offset;           // start of the instance in a batched state (doubles)
   double dx, dy;
   int bcx, bcy;            // 0 periodic, 1 transmissive
-  const double* alpha_in;  // [2] wave speeds of the stage input state
-  double* alpha_out;       // [2] max-accumulators for the stage output state
+  const double* alpha_in;  // ALPHA_SET: wave speeds of the stage input state
+  double* alpha_out;       // ALPHA_SET: max-accumulators for the stage output state
   const double* dt;        // time step of the current step
   const int* done;         // instance finished (fam_run), may be null
   // double Mach reflection boundaries (dmr != 0): the boundary time of a launch is
@@ -89,9 +89,20 @@ struct OEArgs {
   double* delta_out;       // single instance, test export: delta per cell (NULL: not written)
 };
 
+// A wave-speed maximum (x, y) is accumulated by atomics in ALPHA_SLOTS slots, one
+// cache line apart; its readers take the largest.  Device atomics are executed at
+// the memory side, one cache line at a time: a wave's two cost 24 ns on a shared
+// pair, which bounded launches of many short waves (1024 waves: 24.5 us, on 32
+// slots a line apart 3.0 us of which 2.6 are the launch; 16 slots 3.0, and 4.9
+// against 2.9 at 2048 waves; 32 slots packed in 4 lines 6.2).
+constexpr int ALPHA_SLOTS = 32;
+constexpr int ALPHA_STRIDE = 16;                          // doubles: 128 B
+constexpr int ALPHA_SET = ALPHA_SLOTS * ALPHA_STRIDE;     // one maximum (x, y)
+constexpr int ALPHA_INST = 6 * ALPHA_SET;                 // of an instance: [parity][stage input 0..2]
+
 // per-instance step bookkeeping (device)
 struct StepState {
-  double alpha[2][3][2];   // [parity][stage input 0..2][x/y]
+  double* alpha;           // [parity][stage input 0..2][ALPHA_SET]
   double dt;               // time step of the current step
   double t;                // time reached: the context clock (0 at set-up, advanced by every step)
   double t_final;          // <= 0: none
@@ -140,7 +151,6 @@ void launch_alpha1d(int sys, const PhysParams& pp, const double* U, const Inst& 
 
 // step bookkeeping: dt, clipping, termination, zeroing of the accumulators
 void launch_step_begin(StepState* st, int ninst, int parity, double dt_fixed, double t_final, hipStream_t s);
-void launch_zero_alpha(StepState* st, int ninst, int parity, hipStream_t s);
 // per run: wave-speed slots, dt, step count and termination back to zero; the
 // time (the context clock) is kept
 void launch_reset_steps(StepState* st, int ninst, double t_final, double dt_fixed, hipStream_t s);

@@ -41,11 +41,12 @@ constexpr size_t OFF_PARTIAL = 1536;      // Type I: per-block partial sums (4 x
 constexpr int T1_BLOCKS = 256;
 constexpr size_t OFF_TILES = 10240;       // limiter: tile order (ntiles + 1) and work (ntiles) ints
 constexpr size_t TILE_BYTES = 128 * 1024;
+constexpr size_t OFF_ALPHA = OFF_TILES + TILE_BYTES;   // wave-speed slots
 constexpr size_t OFF_W = 256 * 1024;      // W1, W2: two stage states
 static_assert(sizeof(StepState) <= OFF_FLAG - OFF_ST, "StepState slot");
 static_assert(sizeof(Inst) <= OFF_STATS - OFF_AINST, "Inst slot");
 static_assert(OFF_PARTIAL + 4 * T1_BLOCKS * sizeof(double) <= OFF_TILES, "Type I slots");
-static_assert(OFF_TILES + TILE_BYTES <= OFF_W, "tile slots");
+static_assert(OFF_ALPHA + fam::ALPHA_INST * sizeof(double) <= OFF_W && OFF_ALPHA % 128 == 0, "wave-speed slots");
 static_assert(FAM_STATIC_SCRATCH_BYTES % 256 == 0 && OFF_W % 256 == 0, "alignment");
 
 constexpr int MAX_DEVICES = 64;
@@ -73,6 +74,10 @@ __global__ void static_init_kernel(StepState* st, StepState s0, Inst* ainst, Ins
     *st = s0;
     *ainst = a0;
     *flag = 0;
+  }
+  for (int k = threadIdx.x; k < 6 * fam::ALPHA_SLOTS; k += blockDim.x) {
+    double* slot = s0.alpha + k * fam::ALPHA_STRIDE;
+    slot[0] = slot[1] = 0.0;
   }
 }
 
@@ -136,6 +141,8 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   in.done = &st->done;
   in.t_end = &st->t;
   StepState s0{};
+  s0.alpha = reinterpret_cast<double*>(base + OFF_ALPHA);
+  auto alpha = [&](int p, int q) { return s0.alpha + (3 * p + q) * fam::ALPHA_SET; };
   s0.cfl = f.cfl;
   const double e = f.dt_rule == 1 ? f.k / 3.0 : 1.0;
   s0.hx = std::pow(in.dx, e);
@@ -143,8 +150,8 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   s0.dim = dim;
   s0.t = t;
   Inst a0 = in;
-  a0.alpha_in = &st->alpha[0][0][0];
-  a0.alpha_out = &st->alpha[0][0][0];
+  a0.alpha_in = alpha(0, 0);
+  a0.alpha_out = alpha(0, 0);
   hipLaunchKernelGGL(static_init_kernel, dim3(1), dim3(64), 0, s, st, s0, ainst, a0,
                      reinterpret_cast<int*>(base + OFF_FLAG));
   if (f.pp) fam::launch_tile_identity(tile_perm, tile_work, ntiles, s);
@@ -174,8 +181,8 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
     A.tile_work = tile_work;
     A.row_cost = nullptr;
     Inst is = in;
-    is.alpha_in = &st->alpha[0][k_s][0];
-    is.alpha_out = k_s < 2 ? &st->alpha[0][k_s + 1][0] : &st->alpha[1][0][0];
+    is.alpha_in = alpha(0, k_s);
+    is.alpha_out = k_s < 2 ? alpha(0, k_s + 1) : alpha(1, 0);
     is.t_ofs = k_s == 0 ? 1.0 : k_s == 2 ? 0.5 : 0.0;
     if (dim == 1)
       fam::launch_stage1d(f.k, f.system, A, is, s);
@@ -208,7 +215,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
     A.flag = flag;
     A.done = &st->done;
     Inst io = in;
-    io.alpha_in = &st->alpha[0][0][0];
+    io.alpha_in = alpha(0, 0);
     io.alpha_out = nullptr;
     io.t_ofs = 0.0;
     if (f.oe == FAM_OE_TYPE1) fam::launch_type1_stats(W1, io, nc, nmom, partial, T1_BLOCKS, dmax, stats, s);
