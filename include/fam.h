@@ -195,8 +195,10 @@ fam_status fam_autotune(fam_ctx* ctx, const double* U, int reps, int* choice);
  * that fam_autotune returned earlier): stage_H = strip-tile height of the RK
  * stage kernel, or 0 for the segment list of a limiter-on context (each strip
  * cut into segments of equal cost, recorded per row by the previous stage
- * launch; one round of waves); oe_H = tile height of the OE kernel.  Results
- * are unchanged by the choice (bitwise).  Captured step graphs are dropped.
+ * launch; one round of waves); oe_H = tile height of the OE kernel.  On meshes
+ * too small to fill the GPU with tiles of 8 rows a launch takes fewer rows than
+ * the height set here or tuned.  Results are unchanged by the choice (bitwise).
+ * Captured step graphs are dropped.
  * FAM_ERR_ARG for a NULL context, heights outside [8, ny] (or [1, ny] when ny <
  * 8) or stage_H = 0 without the limiter (or with more strips than wave slots);
  * FAM_ERR_STATE for 1D or batched contexts.  Asynchronous. */

@@ -113,14 +113,6 @@ Inst inst_for(const fam_ctx* c, int i, int parity, int stage) {
   return in;
 }
 
-// rows per strip tile: enough tiles to fill 256 CUs several times over
-int choose_H(int nx, int ny) {
-  const int strips = (nx + fam::STRIP - 1) / fam::STRIP;
-  int H = 32;
-  while (H > 8 && (size_t)strips * ((ny + H - 1) / H) < 8 * 256) H /= 2;
-  return std::min(H, std::max(ny, 1));
-}
-
 static fam_status init_segments(fam_ctx* c);
 
 static fam_status alloc_common(fam_ctx* c) {
@@ -260,8 +252,14 @@ extern "C" fam_status fam_init(const fam_config* cfg, void* hip_stream, fam_ctx*
   c->offsets = {0};
   c->max_cells = (size_t)f.nx * (f.dim == 2 ? f.ny : 1);
   c->len = c->max_cells * c->nc * c->nmom;
-  c->H = f.dim == 2 ? choose_H(f.nx, f.ny) : 1;
-  c->H_oe = c->H;
+  c->H = c->H_oe = 1;
+  if (f.dim == 2) {
+    const int ms = fam::stage_rows(f.nx, f.ny, f.k, c->nc, f.char_vars != 0), mo = fam::oe_rows(f.nx, f.ny, c->nc);
+    c->H = std::min(std::max(ms, 8), f.ny);
+    c->H_oe = std::min(std::max(mo, 8), f.ny);
+    c->H_most = ms < 8 ? ms : 0;
+    c->H_oe_most = mo < 8 ? mo : 0;
+  }
   fam_status a = alloc_common(c);
   if (a == FAM_OK && f.dim == 2 && c->pp) {
     // tile heights are >= 8 rows (or the whole mesh when ny < 8)
@@ -285,9 +283,22 @@ extern "C" fam_status fam_init(const fam_config* cfg, void* hip_stream, fam_ctx*
 }
 
 // work list of a batch: (instance, i0, j0, H) strip tiles of height min(H, ny),
-// largest instances first (the persistent kernels take them round-robin)
+// largest instances first (the persistent kernels take them round-robin); H is
+// Hmax, or the model's height of a batch so small that this is below 8
 static fam_status build_work_list(fam_ctx* c, int Hmax) {
   const int n = c->ninst;
+  c->batch_H = Hmax;
+  int most_rows = 1;
+  for (const fam_config& f : c->cfg) most_rows = std::max(most_rows, f.ny);
+  const int model = fam::model_rows(
+      [&](int H) {
+        long long tiles = 0;
+        for (const fam_config& f : c->cfg)
+          tiles += (long long)((f.nx + fam::STRIP - 1) / fam::STRIP) * ((f.ny + H - 1) / H);
+        return tiles;
+      },
+      most_rows, fam::stage_waves(c->k, c->nc, false), c->nc == 1 ? 0.3 : 0.45);
+  Hmax = launch_H(Hmax, model < 8 ? model : 0);
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
@@ -322,7 +333,6 @@ static fam_status build_work_list(fam_ctx* c, int Hmax) {
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(c->stream));
   }
-  c->batch_H = Hmax;
   return FAM_OK;
 }
 
@@ -459,7 +469,9 @@ void enqueue_stage(fam_ctx* c, int s, int parity, const double* U0, const double
         fam::launch_partition(c->row_cost, c->row_pref, c->part_state, (f.nx + fam::STRIP - 1) / fam::STRIP, f.ny,
                             c->seg_budget, c->seg, c->nseg, c->stream);
     } else {
-      fam::launch_stage2d(c->k, c->sys, A, in, c->H, c->stream);
+      const int H = launch_H(c->H, c->H_most);
+      if (H < c->H) A.tile_perm = nullptr;   // the order is that of the tiles of height H
+      fam::launch_stage2d(c->k, c->sys, A, in, H, c->stream);
     }
   } else {
     fam::launch_stage2d_batched(c->k, c->sys, A, c->d_insts[parity][s], c->d_work, c->nwork, c->pblocks, c->stream);
@@ -489,7 +501,7 @@ void enqueue_oe(fam_ctx* c, int parity, const double* Un, double* Uout, const do
     if (c->dim == 1)
       fam::launch_oe1d(c->k, c->sys, A, in, c->stream);
     else
-      fam::launch_oe2d(c->k, c->sys, A, in, c->H_oe, c->stream);
+      fam::launch_oe2d(c->k, c->sys, A, in, launch_H(c->H_oe, c->H_oe_most), c->stream);
   } else {
     fam::launch_oe2d_batched(c->k, c->sys, A, c->d_insts[parity][3], c->d_work, c->nwork, c->pblocks, c->stream);
   }

@@ -30,8 +30,10 @@ struct fam_ctx {
   double* partial = nullptr;   // Type I partial sums
   double* dmax = nullptr;
   int t1_blocks = 256;
-  int H = 32;                  // rows per strip tile of the stage kernel (single instance)
-  int H_oe = 32;               // rows per strip tile of the OE kernel (single instance)
+  // rows per strip tile (single instance): the set or tuned heights, at least 8; the
+  // launches of a mesh so small that the model asks for fewer than 8 take the model's
+  int H = 32, H_oe = 32;       // stage and OE kernel
+  int H_most = 0, H_oe_most = 0;   // the model's height where below 8, else no bound (0)
   // limiter on: order of the stage kernel's tiles (single instance) or work-list
   // items (batch), and the limiter work per tile / item of its last launch
   int* tile_perm = nullptr;
@@ -74,7 +76,8 @@ struct fam_ctx {
 
 fam_status validate_config(const fam_config& c);
 double default_gamma_k(int dim, int k);
-int choose_H(int nx, int ny);   // default strip-tile height of a 2D mesh
+// rows per tile of a launch: H, or the model's `most` where that bounds it
+inline int launch_H(int H, int most) { return most > 0 && most < H ? most : H; }
 fam_status set_stage_H(fam_ctx* c, int H);
 fam::Inst inst_for(const fam_ctx* c, int i, int parity, int stage);
 fam_status reset_steps(fam_ctx* c, double t_final, double dt_fixed);

@@ -16,6 +16,48 @@ __host__ __device__ constexpr int stage_waves(int k, int nc, bool charv) {
   return nc == 1 ? 4 : (k >= 6 || charv) ? 1 : 2;
 }
 
+constexpr int SIMDS = 1024;   // 256 CUs x 4
+
+// Rows per strip tile from a model of a launch of tiles(H) waves.  A tile of H rows
+// costs H + 2 row times (it also reconstructs a ring row on either side); w waves
+// on a SIMD take 1 + share (w - 1) times as long as one, up to `waves` of them,
+// and further tiles follow in rounds.  On small meshes the rows' latency decides:
+// one-row tiles on every SIMD; from about a million cells it is the ring rows and
+// the last round.  Measured (us a stage launch at the model's height against the 8
+// rows that were the least before): 40x40 k=4 10.7 / 37.6; 96x80 k=5, limiter 23.5
+// / 64.8; 203x131 k=5 14.3 / 47.6; 256x256 k=6 22.8 / 58.2; 512x512 k=5 37.7 /
+// 52.2 (5 rows); 700x700 k=5 56.9 / 79.8 (5 rows); 1024x1024 k=5 110.7 / 129.9
+// (10 rows); 1201x1000 k=6 167.5 / 180.9 (24 rows).
+template <class F>
+inline int model_rows(F tiles, int ny, int waves, double share) {
+  int best = 1;
+  double least = 1e300;
+  for (int H = 1; H <= std::min(ny, 128); ++H) {
+    const long long w = ((long long)tiles(H) + SIMDS - 1) / SIMDS;   // waves of the fullest SIMD
+    const long long rounds = w / waves, rest = w % waves;
+    const double cost =
+        (H + 2) * ((double)rounds * (1.0 + share * (waves - 1)) + (rest > 0 ? 1.0 + share * (rest - 1) : 0.0));
+    if (cost < least) {
+      least = cost;
+      best = H;
+    }
+  }
+  return best;
+}
+
+// The slowdown of a further wave on a SIMD, from launches of 1, 2, 3 ... waves on
+// each (512x512 and 700x555, 1 to 32 rows): stage 0.45 with two waves of nc = 4, 0.3
+// with four of nc = 1; OE kernel 0.3
+inline int stage_rows(int nx, int ny, int k, int nc, bool charv) {
+  const int strips = (nx + STRIP - 1) / STRIP;
+  return model_rows([&](int H) { return (long long)strips * ((ny + H - 1) / H); }, ny, stage_waves(k, nc, charv),
+                    nc == 1 ? 0.3 : 0.45);
+}
+inline int oe_rows(int nx, int ny, int nc) {
+  const int strips = (nx + STRIP - 1) / STRIP;
+  return model_rows([&](int H) { return (long long)strips * ((ny + H - 1) / H); }, ny, nc == 1 ? 4 : 2, 0.3);
+}
+
 struct PhysParams {
   double gamma, ax, ay;
 };

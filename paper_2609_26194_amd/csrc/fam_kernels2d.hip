@@ -920,12 +920,14 @@ __global__ void FAM_STAGE_ATTR(K, CHAR) stage2d_kernel(StageArgs A, Inst in, int
   bool bad = false;
   int i0, j0, tile = 0;
   if constexpr (PP) {
-    // 1D grid: tiles in the order of the previous launch's limiter work
+    // 1D grid: tiles in the order of the previous launch's limiter work, if any
     const int strips = (in.nx + STRIP - 1) / STRIP;
     // tiles with limiter work first (spread over the XCDs in turn), then the
     // others in the XCD-aware order of their row-major index
     const int N = gridDim.x;
-    tile = __builtin_amdgcn_readfirstlane(A.tile_perm[heavy_first_slot(blockIdx.x, N, A.tile_perm[N])]);
+    tile = A.tile_perm
+               ? __builtin_amdgcn_readfirstlane(A.tile_perm[heavy_first_slot(blockIdx.x, N, A.tile_perm[N])])
+               : xcd_tile(blockIdx.x, N);
     i0 = (tile % strips) * STRIP;
     j0 = (tile / strips) * H;
     S.nwork = 0;
@@ -937,11 +939,9 @@ __global__ void FAM_STAGE_ATTR(K, CHAR) stage2d_kernel(StageArgs A, Inst in, int
   stage_tile<K, P, PP, DMR, CHAR>(phys, A, in, i0, j0, H, S, amx, amy, bad);
   flush_wave_results(amx, amy, bad, in.alpha_out, A.flag);
   if constexpr (PP) {
-    if (threadIdx.x == 0) A.tile_work[tile] = S.nwork;
+    if (threadIdx.x == 0 && A.tile_perm) A.tile_work[tile] = S.nwork;
   }
 }
-
-constexpr int ORDER_MIN_TILES = 1024;   // 256 CUs x 4 SIMDs: one stage wave on each
 
 // tile_perm := tiles with tile_work > 0 first, then the others, each group in
 // index order (one block; each thread owns a contiguous chunk)
@@ -1184,7 +1184,7 @@ __global__ void FAM_STAGE_ATTR(K, false) stage2d_batched_kernel(StageArgs A, con
     if constexpr (PP) S.nwork = 0;
     // slot 0 alone: the atomics of a batch already go to as many lines as it has
     // instances, and the reduction of all slots for every item costs more (40
-    // meshes of 32^2 to 512^2: 1 %; it also takes scalar registers from the rows)
+    // meshes of 64^2 to 512^2: 1 %; it also takes scalar registers from the rows)
     stage_tile<K, P, PP, false, false, false>(phys, A, in, it.y, it.z, it.w, S, amx, amy, bad);
     flush_wave_results<false>(amx, amy, false, in.alpha_out, A.flag);
     if constexpr (PP) {
@@ -1341,14 +1341,14 @@ static bool dmr_of(const Inst& in) {
     return false;
 }
 template <int K, class P, bool DMR, bool CHAR = false>
-static void launch_stage2d_d(const StageArgs& A, const Inst& in, int H, hipStream_t s) {
+static void launch_stage2d_d(StageArgs A, const Inst& in, int H, hipStream_t s) {
   dim3 grid((in.nx + STRIP - 1) / STRIP, (in.ny + H - 1) / H);
   if (A.pp) {
     const int ntiles = grid.x * grid.y;
+    // up to one tile per wave slot of the chip every tile starts at once: no order
+    if (ntiles <= SIMDS * stage_waves(K, P::NC, CHAR)) A.tile_perm = nullptr;
     hipLaunchKernelGGL((stage2d_kernel<K, P, true, DMR, CHAR>), dim3(ntiles), dim3(LANES), 0, s, A, in, H);
-    // up to one tile per wave slot of the chip every tile starts at once: the
-    // order stays the identity set with the tile height
-    if (ntiles > ORDER_MIN_TILES * stage_waves(K, P::NC, CHAR))
+    if (A.tile_perm)
       hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(1024), 0, s, A.tile_work, const_cast<int*>(A.tile_perm),
                          ntiles);
   } else {

@@ -99,9 +99,13 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   const size_t cells = (size_t)f.nx * f.ny;
   const size_t len = cells * nc * nmom;
   if (len > LEN_LIMIT) return FAM_ERR_SIZE;
-  const int H = dim == 2 ? choose_H(f.nx, f.ny) : 1;
-  const int ntiles = dim == 2 ? ((f.nx + fam::STRIP - 1) / fam::STRIP) * ((f.ny + H - 1) / H) : 0;
-  if (f.pp && (size_t)(2 * ntiles + 1) * sizeof(int) > TILE_BYTES) return FAM_ERR_SIZE;
+  // launch shapes of a fresh context; the limiter's tile order where its slot holds it
+  const int strips = (f.nx + fam::STRIP - 1) / fam::STRIP;
+  const int H = dim == 2 ? fam::stage_rows(f.nx, f.ny, f.k, nc, f.char_vars != 0) : 1;
+  const int H_oe = dim == 2 ? fam::oe_rows(f.nx, f.ny, nc) : 1;
+  const int ntiles = dim == 2 ? strips * ((f.ny + H - 1) / H) : 0;
+  const bool order = f.pp && (size_t)(2 * ntiles + 1) * sizeof(int) <= TILE_BYTES;
+  if (f.pp && (2 * (size_t)strips * ((f.ny + 31) / 32) + 1) * sizeof(int) > TILE_BYTES) return FAM_ERR_SIZE;
 
   char* base = nullptr;
   fam_status r = scratch_ptr(&base);
@@ -113,8 +117,8 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   double* stats = reinterpret_cast<double*>(base + OFF_STATS);
   double* dmax = reinterpret_cast<double*>(base + OFF_DMAX);
   double* partial = reinterpret_cast<double*>(base + OFF_PARTIAL);
-  int* tile_perm = reinterpret_cast<int*>(base + OFF_TILES);
-  int* tile_work = tile_perm + (ntiles + 1);
+  int* tile_perm = order ? reinterpret_cast<int*>(base + OFF_TILES) : nullptr;
+  int* tile_work = order ? tile_perm + (ntiles + 1) : nullptr;
   double* W1 = reinterpret_cast<double*>(base + OFF_W);
   double* W2 = W1 + len;
 
@@ -154,7 +158,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   a0.alpha_out = alpha(0, 0);
   hipLaunchKernelGGL(static_init_kernel, dim3(1), dim3(64), 0, s, st, s0, ainst, a0,
                      reinterpret_cast<int*>(base + OFF_FLAG));
-  if (f.pp) fam::launch_tile_identity(tile_perm, tile_work, ntiles, s);
+  if (order) fam::launch_tile_identity(tile_perm, tile_work, ntiles, s);
 
   const fam::PhysParams phys{f.gamma, f.ax, f.ay};
   // wave speeds of U into the stage-0 input slot, then dt and the clock
@@ -222,7 +226,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
     if (dim == 1)
       fam::launch_oe1d(f.k, f.system, A, io, s);
     else
-      fam::launch_oe2d(f.k, f.system, A, io, H, s);
+      fam::launch_oe2d(f.k, f.system, A, io, H_oe, s);
   }
   if (dt_used_dev && hipMemcpyAsync(dt_used_dev, &st->dt, sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess)
     return FAM_ERR_DEVICE;
