@@ -122,9 +122,8 @@ static fam_status alloc_common(fam_ctx* c) {
   if (hipMalloc(&c->st, sizeof(StepState) * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->alpha, sizeof(double) * fam::ALPHA_INST * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->flag, sizeof(int) * 4) != hipSuccess) return FAM_ERR_NOMEM;
-  if (hipMalloc(&c->stats, sizeof(double) * 8 * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
-  if (hipMalloc(&c->partial, sizeof(double) * 4 * c->t1_blocks) != hipSuccess) return FAM_ERR_NOMEM;
-  if (hipMalloc(&c->dmax, sizeof(double) * 8) != hipSuccess) return FAM_ERR_NOMEM;
+  if (hipMalloc(&c->stats, sizeof(double2) * 4 * fam::TYPE1_BLOCKS) != hipSuccess) return FAM_ERR_NOMEM;
+  if (hipMalloc(&c->partial, sizeof(double) * 4 * fam::TYPE1_BLOCKS) != hipSuccess) return FAM_ERR_NOMEM;
   std::vector<int> zero(4, 0);
   HIP_TRY(hipMemcpy(c->flag, zero.data(), sizeof(int) * 4, hipMemcpyHostToDevice));
   return FAM_OK;
@@ -207,7 +206,7 @@ extern "C" void fam_destroy(fam_ctx* c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   destroy_graphs(c);
   fam_adjoint_free(c);
-  void* bufs[] = {c->W1,        c->W2,        c->st,       c->alpha, c->flag, c->stats,    c->partial,  c->dmax,
+  void* bufs[] = {c->W1,        c->W2,        c->st,       c->alpha, c->flag, c->stats,    c->partial,
                   c->d_work,    c->tile_perm, c->tile_work, c->seg,  c->nseg,     c->row_cost, c->row_pref,
                   c->part_state};
   for (void* p : bufs)
@@ -497,7 +496,7 @@ void enqueue_oe(fam_ctx* c, int parity, const double* Un, double* Uout, const do
     Inst in = inst_for(c, 0, parity, 3);
     if (dt_override) in.dt = dt_override;
     if (c->oe == FAM_OE_TYPE1)
-      fam::launch_type1_stats(Un, in, c->nc, c->nmom, c->partial, c->t1_blocks, c->dmax, c->stats, c->stream);
+      fam::launch_type1_stats(Un, in, c->nc, c->nmom, c->partial, c->stats, c->stream);
     if (c->dim == 1)
       fam::launch_oe1d(c->k, c->sys, A, in, c->stream);
     else

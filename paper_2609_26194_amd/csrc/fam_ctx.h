@@ -26,10 +26,8 @@ struct fam_ctx {
   fam::StepState* st = nullptr;
   double* alpha = nullptr;     // wave-speed slots, ALPHA_INST per instance
   int* flag = nullptr;
-  double* stats = nullptr;     // Type I: [inst*8 + ...]
-  double* partial = nullptr;   // Type I partial sums
-  double* dmax = nullptr;
-  int t1_blocks = 256;
+  double2* stats = nullptr;    // Type I: maxima per block
+  double* partial = nullptr;   // Type I: sums per block
   // rows per strip tile (single instance): the set or tuned heights, at least 8; the
   // launches of a mesh so small that the model asks for fewer than 8 take the model's
   int H = 32, H_oe = 32;       // stage and OE kernel

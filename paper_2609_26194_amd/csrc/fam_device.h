@@ -364,6 +364,20 @@ __device__ __forceinline__ double* alpha_slot(double* set, unsigned wave) {
   return set + (wave & (ALPHA_SLOTS - 1)) * ALPHA_STRIDE;
 }
 
+// Type I: D_Omega and eps_Omega of component c from the blocks' maxima (every lane)
+__device__ __forceinline__ void type1_bounds(const double2* __restrict__ stats, const Inst& in, int c, double& D,
+                                             double& eps) {
+  const int nb = type1_blocks((size_t)in.nx * in.ny);
+  double d = 0.0, a = 0.0;
+  for (int b = threadIdx.x & 63; b < nb; b += 64) {
+    const double2 v = stats[b * 4 + c];
+    d = fmax(d, v.x);
+    a = fmax(a, v.y);
+  }
+  D = wave_max(d);
+  eps = 1e-14 * fmax(wave_max(a), 1.0);
+}
+
 // ghost-cell index map: periodic wrap or transmissive clamp
 __device__ __forceinline__ int ghost(int i, int n, int bc) {
   if (bc == 0) {

@@ -125,7 +125,7 @@ struct OEArgs {
   double gamma_k;
   int type;                // 1 or 2
   int k6_table;
-  const double* stats;     // Type I: [inst*8 + c] D_Omega, [inst*8 + 4 + c] eps_Omega
+  const double2* stats;    // Type I: [block*4 + c] of type1_blocks(cells) blocks: max |u - mean|, max |u|
   int* flag;
   const int* done;
   double* delta_out;       // single instance, test export: delta per cell (NULL: not written)
@@ -183,8 +183,14 @@ void launch_oe2d_batched(int k, int sys, const OEArgs& A, const Inst* insts, con
 void launch_alpha2d(int sys, const PhysParams& pp, const double* U, const Inst* insts, int ninst,
                     size_t max_cells, int* flag, hipStream_t s);
 // Type I reference quantities of one instance (nmom = moments per component)
-void launch_type1_stats(const double* U, const Inst& in, int nc, int nmom, double* partial, int nblocks,
-                        double* dmax, double* stats, hipStream_t s);
+// Type I statistics: partial (TYPE1_BLOCKS * 4 sums) and stats (TYPE1_BLOCKS * 4 pairs of maxima) of one entry
+// per block and component, which the OE kernels reduce themselves.  256 cells a block up to one block per CU
+constexpr int TYPE1_BLOCKS = 256;
+__host__ __device__ inline int type1_blocks(size_t cells) {
+  return cells >= (size_t)TYPE1_BLOCKS * 256 ? TYPE1_BLOCKS : (int)((cells + 255) / 256);
+}
+void launch_type1_stats(const double* U, const Inst& in, int nc, int nmom, double* partial, double2* stats,
+                        hipStream_t s);
 
 // 1D
 void launch_stage1d(int k, int sys, const StageArgs& A, const Inst& in, hipStream_t s);

@@ -195,6 +195,11 @@ __global__ void __launch_bounds__(T1) oe1d_kernel(OEArgs A, Inst in) {
   const int i = i0 - 1 + t;
   const double dt = *in.dt;
   load_tile1<NC>(S, A.Un, in, i0);
+  double D1[NC], eps1[NC];
+  if (A.type != 2) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) type1_bounds(A.stats, in, c, D1[c], eps1[c]);
+  }
   __syncthreads();
   double lt[NC];
 #pragma unroll
@@ -224,8 +229,8 @@ __global__ void __launch_bounds__(T1) oe1d_kernel(OEArgs A, Inst in) {
         D = fmax(fmax(fabs(a - Ssum), fabs(b - Ssum)), fabs(d - Ssum));
         eps = 1e-14 * fmax(fmax(fmax(fabs(a), fabs(b)), fabs(d)), 1.0);
       } else {
-        D = A.stats[in.id * 8 + c];
-        eps = A.stats[in.id * 8 + 4 + c];
+        D = D1[c];
+        eps = eps1[c];
       }
       const double s = (D < eps) ? 0.0 : A.gamma_k * J / D;
       sig = fmax(sig, s);

@@ -35,18 +35,17 @@ static __device__ __align__(256) double scratch[FAM_STATIC_SCRATCH_BYTES / sizeo
 constexpr size_t OFF_ST = 0;              // StepState
 constexpr size_t OFF_FLAG = 256;          // internal non-physical flag (int)
 constexpr size_t OFF_AINST = 512;         // Inst record of the 2D wave-speed reduction
-constexpr size_t OFF_STATS = 1024;        // Type I: D_Omega, eps_Omega per component
-constexpr size_t OFF_DMAX = 1280;         // Type I: maxima
-constexpr size_t OFF_PARTIAL = 1536;      // Type I: per-block partial sums (4 x T1_BLOCKS)
-constexpr int T1_BLOCKS = 256;
+constexpr size_t OFF_PARTIAL = 1536;      // Type I: sums per block
 constexpr size_t OFF_TILES = 10240;       // limiter: tile order (ntiles + 1) and work (ntiles) ints
 constexpr size_t TILE_BYTES = 128 * 1024;
 constexpr size_t OFF_ALPHA = OFF_TILES + TILE_BYTES;   // wave-speed slots
+constexpr size_t OFF_STATS = OFF_ALPHA + fam::ALPHA_INST * sizeof(double);   // Type I: maxima per block
 constexpr size_t OFF_W = 256 * 1024;      // W1, W2: two stage states
 static_assert(sizeof(StepState) <= OFF_FLAG - OFF_ST, "StepState slot");
-static_assert(sizeof(Inst) <= OFF_STATS - OFF_AINST, "Inst slot");
-static_assert(OFF_PARTIAL + 4 * T1_BLOCKS * sizeof(double) <= OFF_TILES, "Type I slots");
-static_assert(OFF_ALPHA + fam::ALPHA_INST * sizeof(double) <= OFF_W && OFF_ALPHA % 128 == 0, "wave-speed slots");
+static_assert(sizeof(Inst) <= OFF_PARTIAL - OFF_AINST, "Inst slot");
+static_assert(OFF_PARTIAL + 4 * fam::TYPE1_BLOCKS * sizeof(double) <= OFF_TILES, "Type I sums");
+static_assert(OFF_ALPHA % 128 == 0, "wave-speed slots");
+static_assert(OFF_STATS + 4 * fam::TYPE1_BLOCKS * sizeof(double2) <= OFF_W, "Type I maxima");
 static_assert(FAM_STATIC_SCRATCH_BYTES % 256 == 0 && OFF_W % 256 == 0, "alignment");
 
 constexpr int MAX_DEVICES = 64;
@@ -114,8 +113,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   StepState* st = reinterpret_cast<StepState*>(base + OFF_ST);
   int* flag = flag_dev ? flag_dev : reinterpret_cast<int*>(base + OFF_FLAG);
   Inst* ainst = reinterpret_cast<Inst*>(base + OFF_AINST);
-  double* stats = reinterpret_cast<double*>(base + OFF_STATS);
-  double* dmax = reinterpret_cast<double*>(base + OFF_DMAX);
+  double2* stats = reinterpret_cast<double2*>(base + OFF_STATS);
   double* partial = reinterpret_cast<double*>(base + OFF_PARTIAL);
   int* tile_perm = order ? reinterpret_cast<int*>(base + OFF_TILES) : nullptr;
   int* tile_work = order ? tile_perm + (ntiles + 1) : nullptr;
@@ -222,7 +220,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
     io.alpha_in = alpha(0, 0);
     io.alpha_out = nullptr;
     io.t_ofs = 0.0;
-    if (f.oe == FAM_OE_TYPE1) fam::launch_type1_stats(W1, io, nc, nmom, partial, T1_BLOCKS, dmax, stats, s);
+    if (f.oe == FAM_OE_TYPE1) fam::launch_type1_stats(W1, io, nc, nmom, partial, stats, s);
     if (dim == 1)
       fam::launch_oe1d(f.k, f.system, A, io, s);
     else
