@@ -526,15 +526,26 @@ void enqueue_step(fam_ctx* c, double* U, int parity, double dt_fixed, double t_f
   }
 }
 
+// 1D meshes that run in one workgroup: a whole chunk of steps is one launch
+static bool small_1d(const fam_ctx* c) { return c->dim == 1 && c->cfg[0].nx <= fam::run1d_max(c->nc); }
+static void enqueue_small_1d(fam_ctx* c, double* U, int nsteps, bool fresh, double dt_fixed, double t_final) {
+  fam::launch_run1d(c->k, c->sys, c->phys, U, make_inst(c, 0), c->st, c->flag, nsteps, fresh, dt_fixed, t_final, c->oe,
+                    c->gamma_k, c->stream);
+}
+
 // ---------------------------------------------------------------------------
 // public entry points
 // ---------------------------------------------------------------------------
 extern "C" fam_status fam_step(fam_ctx* c, double* U, double dt_fixed, double* dt_used_dev) {
   if (!c || !U) return FAM_ERR_ARG;
-  fam_status r = reset_steps(c, 0.0, 0.0);
-  if (r != FAM_OK) return r;
-  enqueue_alpha_full(c, U, 0);
-  enqueue_step(c, U, 0, dt_fixed, 0.0);
+  if (small_1d(c)) {
+    enqueue_small_1d(c, U, 1, true, dt_fixed, 0.0);
+  } else {
+    fam_status r = reset_steps(c, 0.0, 0.0);
+    if (r != FAM_OK) return r;
+    enqueue_alpha_full(c, U, 0);
+    enqueue_step(c, U, 0, dt_fixed, 0.0);
+  }
   if (dt_used_dev) {
     for (int i = 0; i < c->ninst; ++i)
       HIP_TRY(hipMemcpyAsync(dt_used_dev + i, &c->st[i].dt, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -782,10 +793,14 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
   if (!c || !U || max_steps < 0) return FAM_ERR_ARG;
   if (!(t_final > 0.0) && max_steps == 0) return FAM_ERR_ARG;
   const int limit = max_steps > 0 ? max_steps : 0x7fffffff;
-  fam_status r = reset_steps(c, t_final > 0 ? t_final : 0.0, dt_fixed);
-  if (r != FAM_OK) return r;
-  enqueue_alpha_full(c, U, 0);
   const double tf = t_final > 0 ? t_final : 0.0;
+  const bool small = small_1d(c);
+  fam_status r = FAM_OK;
+  if (!small) {
+    r = reset_steps(c, tf, dt_fixed);
+    if (r != FAM_OK) return r;
+    enqueue_alpha_full(c, U, 0);
+  }
   int launched = 0;
   std::vector<StepState> h(c->ninst);
   int done_steps = 0;
@@ -793,11 +808,15 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
   // With an end time, the first chunk is two steps; each later chunk holds the
   // steps still needed at the last step's dt (at most 64, rounded up to even), so
   // few replays past the end time are no-ops.
-  int next = tf > 0 ? 2 : limit;
+  // A small 1D mesh ends its run inside the kernel: a chunk (one launch) of up to
+  // 1024 steps keeps a launch within some milliseconds.
+  int next = small ? 1024 : tf > 0 ? 2 : limit;
   while (launched < limit) {
     const int chunk = std::min(limit - launched, next);
     const int pairs = chunk / 2;
-    if (c->use_graph && pairs > 0) {
+    if (small) {
+      enqueue_small_1d(c, U, chunk, launched == 0, dt_fixed, tf);
+    } else if (c->use_graph && pairs > 0) {
       hipGraphExec_t ex;
       r = get_graph(c, U, dt_fixed, tf, &ex);
       if (r != FAM_OK) return r;
@@ -808,7 +827,7 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
         enqueue_step(c, U, 1, dt_fixed, tf);
       }
     }
-    if (chunk % 2) enqueue_step(c, U, 0, dt_fixed, tf);
+    if (chunk % 2 && !small) enqueue_step(c, U, 0, dt_fixed, tf);
     launched += chunk;
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(h.data(), c->st, sizeof(StepState) * c->ninst, hipMemcpyDeviceToHost, c->stream));
@@ -834,6 +853,7 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
       return FAM_ERR_NONPHYSICAL;
     }
     if (tf > 0 && all_done) break;
+    if (small) continue;
     if (chunk % 2) break;   // parity would break on another chunk; odd chunks only end a run
     if (tf > 0) {
       const int want = need > 62.0 ? 64 : std::max(2, (int)need);

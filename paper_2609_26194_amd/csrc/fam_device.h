@@ -259,13 +259,14 @@ struct Euler {
   };
   __device__ __forceinline__ void face(int d, const double* u, double a, double* o) const {
     const double inv = rcp(u[0]);
-    const double ke = fma(u[2], u[2], u[1] * u[1]);
-    const double p = g1 * fma(-0.5, ke * inv, u[3]);
+    double ke = u[1] * u[1];
+    if constexpr (DIM == 2) ke = fma(u[2], u[2], ke);
+    const double p = g1 * fma(-0.5, ke * inv, u[NC - 1]);
     const double vel = u[1 + d] * inv, va = vel + a;
     o[0] = fma(a, u[0], u[1 + d]);
     o[1 + d] = fma(u[1 + d], va, p);
-    o[2 - d] = u[2 - d] * va;
-    o[3] = fma(u[3], va, p * vel);
+    if constexpr (DIM == 2) o[2 - d] = u[2 - d] * va;
+    o[NC - 1] = fma(u[NC - 1], va, p * vel);
   }
   __device__ __forceinline__ void volume(const double* u, double w, Volume& V) const {
     const double inv = rcp(u[0]);

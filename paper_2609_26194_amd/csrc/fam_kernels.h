@@ -194,6 +194,11 @@ void launch_type1_stats(const double* U, const Inst& in, int nc, int nmom, doubl
 
 // 1D
 void launch_stage1d(int k, int sys, const StageArgs& A, const Inst& in, hipStream_t s);
+// largest 1D mesh that runs in one workgroup: a lane per cell and per ghost on either
+// side; the 1D Euler kernel needs more than the 128 registers a lane of 1024 may have
+__host__ __device__ constexpr int run1d_max(int nc) { return nc == 1 ? 1022 : 510; }
+void launch_run1d(int k, int sys, const PhysParams& pp, double* U, const Inst& in, StepState* st, int* flag,
+                  int nsteps, bool fresh, double dt_fixed, double t_final, int oe, double gamma_k, hipStream_t s);
 void launch_oe1d(int k, int sys, const OEArgs& A, const Inst& in, hipStream_t s);
 void launch_alpha1d(int sys, const PhysParams& pp, const double* U, const Inst& in, int* flag, hipStream_t s);
 
