@@ -145,8 +145,8 @@ fam_status fam_step(fam_ctx* ctx, double* U, double dt_fixed, double* dt_used_de
 /* Advance U in place until the context clock reaches t_final (the last step
  * clipped to land on it; nothing is done if the clock is already there) or
  * until max_steps steps, whichever comes first (t_final <= 0: max_steps steps).
- * dt_fixed > 0 replaces the CFL rule.  Steps are enqueued in chunks replayed
- * from a captured HIP graph; the stream is synchronised between chunks to test
+ * dt_fixed > 0 replaces the CFL rule.  Steps are enqueued in chunks (long ones
+ * from a captured HIP graph); the stream is synchronised between chunks to test
  * for termination and non-physical states.  For a batched context every
  * instance runs to t_final (each with its own dt), and steps_done is the
  * largest per-instance count of this call.  t_done (host, may be NULL): the

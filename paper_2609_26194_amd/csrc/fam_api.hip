@@ -11,8 +11,8 @@
 //   stage2: (W2, U) -> W1 (or -> U when OE is off)  [Type I stats]  OE: W1 -> U
 // The wave speeds of each stage's output are reduced inside the stage kernel;
 // the last stage's are those of the next step's state (OE keeps averages), so
-// consecutive steps need no separate reduction pass.  Two consecutive steps
-// (stage-slot parity 0 and 1) are captured once into a HIP graph and replayed.
+// consecutive steps need no separate reduction pass.  Long runs replay a HIP graph
+// of several pairs of steps (stage-slot parity 0 and 1).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -767,6 +767,14 @@ extern "C" fam_status fam_check(fam_ctx* c) {
   return FAM_OK;
 }
 
+// A replay starts and ends with a gap of some 7 us on the device, a launch costs the
+// host 4 to 5 us, and a graph of 8 steps 110 us to capture and instantiate.  us a step
+// in runs of 60 steps on a new buffer / again, as launches, graphs of 2 and of 10 steps:
+// 1D 4000 cells 24.7 / 25.3, 25.6 / 24.4, 24.0 / 21.6; 40x40 45.9 / 45.7, 47.8 / 47.1,
+// 46.1 / 43.7; in runs of 20 steps launches win on a new buffer (26.5, 30.3, 31.3).  So
+// graphs hold 8 steps and are used by chunks of 40 steps or more.
+constexpr int GRAPH_PAIRS = 4, GRAPH_MIN_PAIRS = 20;
+
 static fam_status get_graph(fam_ctx* c, double* U, double dt_fixed, double t_final, hipGraphExec_t* out) {
   fam_ctx::GKey key{U, dt_fixed, t_final};
   auto it = c->graphs.find(key);
@@ -776,8 +784,10 @@ static fam_status get_graph(fam_ctx* c, double* U, double dt_fixed, double t_fin
   }
   hipGraph_t g;
   HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  enqueue_step(c, U, 0, dt_fixed, t_final);
-  enqueue_step(c, U, 1, dt_fixed, t_final);
+  for (int p = 0; p < GRAPH_PAIRS; ++p) {
+    enqueue_step(c, U, 0, dt_fixed, t_final);
+    enqueue_step(c, U, 1, dt_fixed, t_final);
+  }
   HIP_TRY(hipStreamEndCapture(c->stream, &g));
   hipGraphExec_t ex;
   hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
@@ -816,13 +826,15 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
     const int pairs = chunk / 2;
     if (small) {
       enqueue_small_1d(c, U, chunk, launched == 0, dt_fixed, tf);
-    } else if (c->use_graph && pairs > 0) {
-      hipGraphExec_t ex;
-      r = get_graph(c, U, dt_fixed, tf, &ex);
-      if (r != FAM_OK) return r;
-      for (int p = 0; p < pairs; ++p) HIP_TRY(hipGraphLaunch(ex, c->stream));
     } else {
-      for (int p = 0; p < pairs; ++p) {
+      int p = 0;
+      if (c->use_graph && pairs >= GRAPH_MIN_PAIRS) {
+        hipGraphExec_t ex;
+        r = get_graph(c, U, dt_fixed, tf, &ex);
+        if (r != FAM_OK) return r;
+        for (; p + GRAPH_PAIRS <= pairs; p += GRAPH_PAIRS) HIP_TRY(hipGraphLaunch(ex, c->stream));
+      }
+      for (; p < pairs; ++p) {
         enqueue_step(c, U, 0, dt_fixed, tf);
         enqueue_step(c, U, 1, dt_fixed, tf);
       }
