@@ -125,46 +125,54 @@ __device__ __forceinline__ void gstencil(const double* __restrict__ U, const Adj
     }
 }
 
-// out = J_d(u)^T w for the 2D Euler flux in direction d
-__device__ __forceinline__ void euler_jt(int d, double g, const double* u, const double* w, double* out) {
-  const double inv = rcp(u[0]);
-  const double vx = u[1] * inv, vy = u[2] * inv;
-  const double q2 = vx * vx + vy * vy;
-  const double g1 = g - 1.0;
-  const double p = g1 * (u[3] - 0.5 * u[0] * q2);
-  const double H = (u[3] + p) * inv;
-  const double k = 0.5 * g1 * q2;
-  if (d == 0) {
-    out[0] = (-vx * vx + k) * w[1] - vx * vy * w[2] + vx * (k - H) * w[3];
-    out[1] = w[0] + (3.0 - g) * vx * w[1] + vy * w[2] + (H - g1 * vx * vx) * w[3];
-    out[2] = -g1 * vy * w[1] + vx * w[2] - g1 * vx * vy * w[3];
-    out[3] = g1 * w[1] + g * vx * w[3];
-  } else {
-    out[0] = -vx * vy * w[1] + (-vy * vy + k) * w[2] + vy * (k - H) * w[3];
-    out[1] = vy * w[1] - g1 * vx * w[2] - g1 * vx * vy * w[3];
-    out[2] = w[0] + vx * w[1] + (3.0 - g) * vy * w[2] + (H - g1 * vy * vy) * w[3];
-    out[3] = g1 * w[2] + g * vy * w[3];
+// What the transposed flux Jacobians share at a point: velocities, enthalpy
+// H = (E + p)/rho = g E/rho - k and k = (g - 1) |v|^2 / 2.
+struct EulerPoint {
+  double vx, vy, k, H;
+  __device__ __forceinline__ EulerPoint(double g, double g1h, const double* u) {
+    const double inv = rcp(u[0]);
+    vx = u[1] * inv;
+    vy = u[2] * inv;
+    k = g1h * fma(vx, vx, vy * vy);
+    H = fma(g, u[3] * inv, -k);
   }
+};
+
+// out = J_d(u)^T w for the 2D Euler flux in direction d: the gradient of
+// w.f(u) = w0 m + rho vd (w.v) + p P + E q with q = w3 vd, P = w_d + q.
+__device__ __forceinline__ void euler_jt(int d, double g1, const EulerPoint& e, const double* w, double* out) {
+  const double vd = d == 0 ? e.vx : e.vy, vo = d == 0 ? e.vy : e.vx;
+  const double wd = w[1 + d], wo = w[2 - d];
+  const double q = w[3] * vd, P = wd + q, t = g1 * P;
+  const double a = wd * vd, b = fma(wo, vo, a);   // (rho part) / vd
+  out[0] = fma(e.k, P, fma(-e.H, q, -(vd * b)));
+  out[1 + d] = fma(-vd, t, fma(e.H, w[3], w[0] + (a + b)));
+  out[2 - d] = fma(-vo, t, wo * vd);
+  out[3] = q + t;
 }
 
-// out = J_1(u)^T w1 + J_2(u)^T w2 (volume points: both directions share the primitives)
-__device__ __forceinline__ void euler_jt2(double g, const double* u, const double* w1, const double* w2,
-                                          double* out) {
-  const double inv = rcp(u[0]);
-  const double vx = u[1] * inv, vy = u[2] * inv;
-  const double q2 = vx * vx + vy * vy;
-  const double g1 = g - 1.0;
-  const double p = g1 * (u[3] - 0.5 * u[0] * q2);
-  const double H = (u[3] + p) * inv;
-  const double k = 0.5 * g1 * q2;
-  const double vxy = vx * vy;
-  out[0] = (-vx * vx + k) * w1[1] - vxy * (w1[2] + w2[1]) + vx * (k - H) * w1[3] + (-vy * vy + k) * w2[2] +
-           vy * (k - H) * w2[3];
-  out[1] = w1[0] + (3.0 - g) * vx * w1[1] + vy * (w1[2] + w2[1]) + (H - g1 * vx * vx) * w1[3] -
-           g1 * vx * w2[2] - g1 * vxy * w2[3];
-  out[2] = -g1 * vy * w1[1] + vx * (w1[2] + w2[1]) - g1 * vxy * w1[3] + w2[0] + (3.0 - g) * vy * w2[2] +
-           (H - g1 * vy * vy) * w2[3];
-  out[3] = g1 * (w1[1] + w2[2]) + g * (vx * w1[3] + vy * w2[3]);
+// a cell's weights of the volume points, w1.f(u) + w2.g(u): w1 = mu_x / dx, w2 = mu_y / dy
+struct VolumeWeights {
+  double a0, b0, a3, b3, s, xx, xy, yy;   // s = a1 + b2, xx = 2 a1, xy = a2 + b1, yy = 2 b2
+  __device__ __forceinline__ VolumeWeights(const double (&mu)[4][3], double idx_, double idy)
+      : a0(mu[0][1] * idx_), b0(mu[0][2] * idy), a3(mu[3][1] * idx_), b3(mu[3][2] * idy) {
+    const double a1 = mu[1][1] * idx_, a2 = mu[2][1] * idx_, b1 = mu[1][2] * idy, b2 = mu[2][2] * idy;
+    s = a1 + b2;
+    xx = 2.0 * a1;
+    xy = a2 + b1;
+    yy = 2.0 * b2;
+  }
+};
+
+// out = J_1(u)^T w1 + J_2(u)^T w2
+__device__ __forceinline__ void euler_jt2(double g1, const EulerPoint& e, const VolumeWeights& w, double* out) {
+  const double q = fma(w.b3, e.vy, w.a3 * e.vx), P = w.s + q, t = g1 * P;
+  const double Qx = fma(w.xy, e.vy, w.xx * e.vx), Qy = fma(w.yy, e.vy, w.xy * e.vx);
+  const double Q2 = fma(e.vy, Qy, e.vx * Qx);
+  out[0] = fma(e.k, P, fma(-e.H, q, -0.5 * Q2));
+  out[1] = fma(-e.vx, t, fma(e.H, w.a3, w.a0 + Qx));
+  out[2] = fma(-e.vy, t, fma(e.H, w.b3, w.b0 + Qy));
+  out[3] = q + t;
 }
 
 // gradient of |u_d| + sqrt(g p / rho) with respect to (rho, m, n, E)
@@ -208,17 +216,14 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // of a group come from four parity sums of the coefficients, and the transposed
 // evaluation from four signed sums of the point adjoints.
 // ---------------------------------------------------------------------------
-// face adjoint weights of the face between cells L (left / below) and R:
-// d J / d Fbar and d J / d Ftil (x-face), d J / d Gbar and d J / d Gtil (y-face)
-__device__ __forceinline__ void face_adj(bool xface, const double (&muL)[3], const double (&muR)[3], double inv,
+// half the face adjoint weights of the face between cells L (left / below) and R:
+// d J / d Fbar and d J / d Ftil (x-face), d J / d Gbar and d J / d Gtil (y-face);
+// hinv = 1 / (2 dx) or 1 / (2 dy)
+__device__ __forceinline__ void face_adj(bool xface, const double (&muL)[3], const double (&muR)[3], double hinv,
                                          double& B, double& T) {
-  if (xface) {
-    B = (-muL[0] - 0.5 * muL[1] + muR[0] - 0.5 * muR[1]) * inv;
-    T = (-muL[2] + muR[2]) * inv;
-  } else {
-    B = (-muL[0] - 0.5 * muL[2] + muR[0] - 0.5 * muR[2]) * inv;
-    T = (-muL[1] + muR[1]) * inv;
-  }
+  const int n = xface ? 1 : 2, q = xface ? 2 : 1;
+  B = fma(-0.5, muL[n] + muR[n], muR[0] - muL[0]) * hinv;
+  T = (muR[q] - muL[q]) * hinv;
 }
 
 template <int TC>
@@ -230,10 +235,11 @@ __device__ __forceinline__ void tile_mu(const double (&tl)[12][TC], int pos, dou
 }
 
 // G: group index; for face groups B/T hold [side][c] for the two faces of the group
-// (side 0: sign +1 face, side 1: sign -1 face)
+// (side 0: sign +1 face, side 1: sign -1 face).  The quadrature weight of a group is
+// folded into the constants of the scatter.
 template <int K, int G>
-__device__ __forceinline__ void coef_group(double g, const double (&cf)[4][ncoef2d(K)], double (&ab)[4][ncoef2d(K)],
-                                           const double (&mu)[4][3], double idx_, double idy,
+__device__ __forceinline__ void coef_group(double g, double g1, const double (&cf)[4][ncoef2d(K)],
+                                           double (&ab)[4][ncoef2d(K)], const VolumeWeights& vw,
                                            const double (&B)[2][4], const double (&T)[2][4], double al,
                                            double& pa) {
   constexpr int NCF = ncoef2d(K);
@@ -241,54 +247,42 @@ __device__ __forceinline__ void coef_group(double g, const double (&cf)[4][ncoef
   constexpr int NXI = G < 2 ? 2 : G < 4 ? (G - 2) : ((G - 4) & 1);
   constexpr int NYI = G < 2 ? G : G < 4 ? 2 : ((G - 4) >> 1);
   constexpr bool XF = G < 2, YF = (G >= 2 && G < 4);
-  double u[4][4];   // [point][component]
+  const double g1h = 0.5 * g1;
+  double v[4][4];   // [component][point]
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    double P[4];
-    parity_sums<NXI, NYI>(cf[c], P, Seq{});
-#pragma unroll
-    for (int s = 0; s < 4; ++s) u[s][c] = P[0] + grp_sx(s) * P[1] + grp_sy(s) * P[2] + grp_sx(s) * grp_sy(s) * P[3];
-  }
+  for (int c = 0; c < 4; ++c) group_values<NXI, NYI, NCF>(cf[c], v[c]);
   double ub[4][4];
+  double sum = 0.0;
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
+    const double u[4] = {v[0][s], v[1][s], v[2][s], v[3][s]};
+    const EulerPoint e(g, g1h, u);
     if constexpr (XF || YF) {
       // face point: side by the sign across the face, Gauss node by the sign along it
       const int side = XF ? (grp_sx(s) > 0 ? 0 : 1) : (grp_sy(s) > 0 ? 0 : 1);
       const double eta = XF ? grp_sy(s) * (NYI == 0 ? GS0 : GS1) : grp_sx(s) * (NXI == 0 ? GS0 : GS1);
-      const double w = XF ? (NYI == 0 ? GW0 : GW1) : (NXI == 0 ? GW0 : GW1);
-      const double sgn = side == 0 ? 1.0 : -1.0;
-      double Fh[4], half[4], jt[4];
-      double dot = 0.0;
+      double h[4], dot = 0.0;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        Fh[c] = w * (B[side][c] + eta * T[side][c]);
-        half[c] = 0.5 * Fh[c];
-        dot = fma(Fh[c], u[s][c], dot);
+        h[c] = fma(eta, T[side][c], B[side][c]);
+        dot = fma(h[c], u[c], dot);
       }
-      euler_jt(XF ? 0 : 1, g, u[s], half, jt);
+      euler_jt(XF ? 0 : 1, g1, e, h, ub[s]);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) ub[s][c] = jt[c] + sgn * 0.5 * al * Fh[c];
-      pa += sgn * 0.5 * dot;
+      for (int c = 0; c < 4; ++c) ub[s][c] = fma(side == 0 ? al : -al, h[c], ub[s][c]);
+      sum = side == 0 ? sum + dot : sum - dot;
     } else {
-      constexpr double w = (NXI == 0 ? GW0 : GW1) * (NYI == 0 ? GW0 : GW1);
-      double w1[4], w2[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        w1[c] = w * mu[c][1] * idx_;
-        w2[c] = w * mu[c][2] * idy;
-      }
-      euler_jt2(g, u[s], w1, w2, ub[s]);
+      euler_jt2(g1, e, vw, ub[s]);
     }
   }
+  constexpr double w = XF ? (NYI == 0 ? GW0 : GW1)
+                          : YF ? (NXI == 0 ? GW0 : GW1) : (NXI == 0 ? GW0 : GW1) * (NYI == 0 ? GW0 : GW1);
+  if constexpr (XF || YF) pa = fma(w, sum, pa);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    double Q[4];
-    Q[0] = ub[0][c] + ub[1][c] + ub[2][c] + ub[3][c];
-    Q[1] = ub[0][c] + ub[1][c] - ub[2][c] - ub[3][c];
-    Q[2] = ub[0][c] - ub[1][c] + ub[2][c] - ub[3][c];
-    Q[3] = ub[0][c] - ub[1][c] - ub[2][c] + ub[3][c];
-    parity_scatter<NXI, NYI>(ab[c], Q, Seq{});
+    const double p = ub[0][c] + ub[1][c], q = ub[2][c] + ub[3][c], r = ub[0][c] - ub[1][c], t = ub[2][c] - ub[3][c];
+    const double Q[4] = {p + q, p - q, r + t, r - t};
+    parity_scatter<NXI, NYI>(ab[c], Q, w, Seq{});
   }
 }
 
@@ -323,9 +317,9 @@ __global__ void __launch_bounds__(CT) adj_coef_kernel(AdjMesh m, const double* _
   __syncthreads();
   double pax = 0.0, pay = 0.0;
   if (inside) {
-    const double g = m.gamma;
+    const double g = m.gamma, g1 = uniform(g - 1.0);
     const double ax = alpha[0], ay = alpha[1];
-    const double idx_ = 1.0 / m.dx, idy = 1.0 / m.dy;
+    const double idx_ = uniform(1.0 / m.dx), idy = uniform(1.0 / m.dy);
     const int base = (ty + 1) * CGX + (tx + 1);   // this cell in the tiles
     double cf[NC][NCF];
 #pragma unroll
@@ -356,42 +350,43 @@ __global__ void __launch_bounds__(CT) adj_coef_kernel(AdjMesh m, const double* _
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int l = 0; l < NCF; ++l) ab[c][l] = 0.0;
+    const VolumeWeights vw(mu, idx_, idy);
     double B[2][4], T[2][4];
     // x-faces: side 0 = right face (this cell on the left), side 1 = left face
     {
       double nb[NC][3];
       tile_mu(tl, base + 1, nb);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) face_adj(true, mu[c], nb[c], idx_, B[0][c], T[0][c]);
+      for (int c = 0; c < NC; ++c) face_adj(true, mu[c], nb[c], 0.5 * idx_, B[0][c], T[0][c]);
       tile_mu(tl, base - 1, nb);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) face_adj(true, nb[c], mu[c], idx_, B[1][c], T[1][c]);
+      for (int c = 0; c < NC; ++c) face_adj(true, nb[c], mu[c], 0.5 * idx_, B[1][c], T[1][c]);
     }
-    coef_group<K, 0>(g, cf, ab, mu, idx_, idy, B, T, ax, pax);
+    coef_group<K, 0>(g, g1, cf, ab, vw, B, T, ax, pax);
     __builtin_amdgcn_sched_barrier(0);
-    coef_group<K, 1>(g, cf, ab, mu, idx_, idy, B, T, ax, pax);
+    coef_group<K, 1>(g, g1, cf, ab, vw, B, T, ax, pax);
     __builtin_amdgcn_sched_barrier(0);
     // y-faces: side 0 = top face (this cell below), side 1 = bottom face
     {
       double nb[NC][3];
       tile_mu(tl, base + CGX, nb);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) face_adj(false, mu[c], nb[c], idy, B[0][c], T[0][c]);
+      for (int c = 0; c < NC; ++c) face_adj(false, mu[c], nb[c], 0.5 * idy, B[0][c], T[0][c]);
       tile_mu(tl, base - CGX, nb);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) face_adj(false, nb[c], mu[c], idy, B[1][c], T[1][c]);
+      for (int c = 0; c < NC; ++c) face_adj(false, nb[c], mu[c], 0.5 * idy, B[1][c], T[1][c]);
     }
-    coef_group<K, 2>(g, cf, ab, mu, idx_, idy, B, T, ay, pay);
+    coef_group<K, 2>(g, g1, cf, ab, vw, B, T, ay, pay);
     __builtin_amdgcn_sched_barrier(0);
-    coef_group<K, 3>(g, cf, ab, mu, idx_, idy, B, T, ay, pay);
+    coef_group<K, 3>(g, g1, cf, ab, vw, B, T, ay, pay);
     __builtin_amdgcn_sched_barrier(0);
-    coef_group<K, 4>(g, cf, ab, mu, idx_, idy, B, T, 0.0, pax);
+    coef_group<K, 4>(g, g1, cf, ab, vw, B, T, 0.0, pax);
     __builtin_amdgcn_sched_barrier(0);
-    coef_group<K, 5>(g, cf, ab, mu, idx_, idy, B, T, 0.0, pax);
+    coef_group<K, 5>(g, g1, cf, ab, vw, B, T, 0.0, pax);
     __builtin_amdgcn_sched_barrier(0);
-    coef_group<K, 6>(g, cf, ab, mu, idx_, idy, B, T, 0.0, pax);
+    coef_group<K, 6>(g, g1, cf, ab, vw, B, T, 0.0, pax);
     __builtin_amdgcn_sched_barrier(0);
-    coef_group<K, 7>(g, cf, ab, mu, idx_, idy, B, T, 0.0, pax);
+    coef_group<K, 7>(g, g1, cf, ab, vw, B, T, 0.0, pax);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < NC; ++c)

@@ -194,8 +194,9 @@ __device__ __forceinline__ void parity_sums(const double* cf, double (&P)[4], st
 }
 
 template <int NXI, int NYI, int... L>
-__device__ __forceinline__ void parity_scatter(double* ab, const double (&Q)[4], std::integer_sequence<int, L...>) {
-  ((ab[L] = fma(phi_node<L, NXI, NYI>(), Q[parity_class<L>()], ab[L])), ...);
+__device__ __forceinline__ void parity_scatter(double* ab, const double (&Q)[4], double w,
+                                               std::integer_sequence<int, L...>) {
+  ((ab[L] = fma(w * phi_node<L, NXI, NYI>(), Q[parity_class<L>()], ab[L])), ...);
 }
 
 // point s of a group: s = 0 (+,+), 1 (+,-), 2 (-,+), 3 (-,-)
