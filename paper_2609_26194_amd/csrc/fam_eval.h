@@ -110,6 +110,80 @@ __device__ __forceinline__ double centre_dot(const double (&u)[27], std::integer
   return v;
 }
 
+// The four values as even and odd parts, p(+-1/2, 0) = ex +- ox, p(0, +-1/2) = ey +- oy,
+// over sums of the stencil that share their parity: with the nine values of a plane
+// numbered from the lower left, c the centre, xs/xd the right plus/minus the left,
+// ys/yd the top and bottom likewise and ss, sd (odd in y), ds (odd in x), dd the corner
+// sums.  A weight of such a sum is the signed mean of its members' weights, which differ
+// by rounding only; 28 products replace 92.
+enum ParitySum { PS_C, PS_XS, PS_XD, PS_YS, PS_YD, PS_SS, PS_SD, PS_DS, PS_DD };
+template <int K, bool FULL>
+struct ParityWeights {
+  double w[4][3][9];   // ex, ox, ey, oy x plane x sum
+};
+template <int K, bool FULL>
+__host__ __device__ constexpr ParityWeights<K, FULL> make_parity_weights() {
+  constexpr CentreWeights cw = make_centre_weights<K, FULL>();
+  // members (sign by stencil position) of the sums
+  const int sg[9][9] = {{0, 0, 0, 0, 1, 0, 0, 0, 0},  {0, 0, 0, 1, 0, 1, 0, 0, 0},  {0, 0, 0, -1, 0, 1, 0, 0, 0},
+                        {0, 1, 0, 0, 0, 0, 0, 1, 0},  {0, -1, 0, 0, 0, 0, 0, 1, 0}, {1, 0, 1, 0, 0, 0, 1, 0, 1},
+                        {-1, 0, -1, 0, 0, 0, 1, 0, 1}, {-1, 0, 1, 0, 0, 0, -1, 0, 1}, {1, 0, -1, 0, 0, 0, -1, 0, 1}};
+  const int xodd[9] = {0, 0, 1, 0, 0, 0, 0, 1, 1}, yodd[9] = {0, 0, 0, 0, 1, 0, 1, 0, 1};
+  ParityWeights<K, FULL> r{};
+  for (int f = 0; f < 4; ++f)
+    for (int m = 0; m < 3; ++m)
+      for (int q = 0; q < 9; ++q) {
+        // parity of the functional against that of the sum, the moment's own included
+        const int px = (xodd[q] + (m == 1)) % 2, py = (yodd[q] + (m == 2)) % 2;
+        if (px != (f == 1) || py != (f == 3)) continue;
+        double v = 0.0;
+        int n = 0;
+        for (int l = 0; l < 9; ++l)
+          if (sg[q][l] != 0) {
+            const int in = m * 9 + l, b = f < 2 ? 0 : 2;
+            const double half = f % 2 == 0 ? 0.5 * (cw.w[b][in] + cw.w[b + 1][in]) : 0.5 * (cw.w[b][in] - cw.w[b + 1][in]);
+            v += sg[q][l] * half;
+            ++n;
+          }
+        r.w[f][m][q] = v / n;
+      }
+  return r;
+}
+template <int K, bool FULL>
+struct ParityTable {
+  static constexpr ParityWeights<K, FULL> t = make_parity_weights<K, FULL>();
+};
+
+// v += w s with w a compile-time constant (skipped when it vanishes to rounding)
+template <int K, bool FULL, int F, int M, int Q>
+__device__ __forceinline__ void parity_acc(double& v, double s) {
+  constexpr double w = ParityTable<K, FULL>::t.w[F][M][Q];
+  if constexpr (w > 1e-15 || w < -1e-15) v = fma(w, s, v);
+}
+template <int K, bool FULL, int F, int M>
+__device__ __forceinline__ void parity_plane(double& v, const double (&s)[9]) {
+  parity_acc<K, FULL, F, M, 0>(v, s[0]);
+  parity_acc<K, FULL, F, M, 1>(v, s[1]);
+  parity_acc<K, FULL, F, M, 2>(v, s[2]);
+  parity_acc<K, FULL, F, M, 3>(v, s[3]);
+  parity_acc<K, FULL, F, M, 4>(v, s[4]);
+  parity_acc<K, FULL, F, M, 5>(v, s[5]);
+  parity_acc<K, FULL, F, M, 6>(v, s[6]);
+  parity_acc<K, FULL, F, M, 7>(v, s[7]);
+  parity_acc<K, FULL, F, M, 8>(v, s[8]);
+}
+__device__ __forceinline__ void parity_sums9(const double (&u)[9], double (&s)[9]) {
+  const double t = u[8] + u[6], td = u[8] - u[6], b = u[2] + u[0], bd = u[2] - u[0];
+  s[PS_C] = u[4];
+  s[PS_XS] = u[5] + u[3];
+  s[PS_XD] = u[5] - u[3];
+  s[PS_YS] = u[7] + u[1];
+  s[PS_YD] = u[7] - u[1];
+  s[PS_SS] = t + b;
+  s[PS_SD] = t - b;
+  s[PS_DS] = td + bd;
+  s[PS_DD] = td - bd;
+}
 
 // ---------------------------------------------------------------------------
 // Transposed reconstruction: RT[in][l] = d c_l / d u_in for the 27 stencil slots

@@ -14,12 +14,12 @@ constexpr int LANES = 64;
 // LDS row window: lane l holds LDS column l = grid column i0 - 2 + l.  Lanes 0
 // and 63 only load; lanes 1 and 62 are ring columns; lanes 2..61 write output.
 // ---------------------------------------------------------------------------
-template <int NPLU>
+template <int NPLU, int SLOTS = 3>
 struct alignas(16) Window {
   // two values before and after the rows: the load-only lanes 0 and 63 read their
   // missing neighbour column there or in the next plane, and nothing uses what
   // they compute from it (two, not one, so that the rows start on 16 bytes)
-  double f[3 * NPLU * LANES + 4];
+  double f[SLOTS * NPLU * LANES + 4];
   __device__ __forceinline__ double& at(int slot, int plane, int col) {
     return f[2 + (slot * NPLU + plane) * LANES + col];
   }
@@ -93,10 +93,10 @@ __device__ __forceinline__ void fetch_row(const double* __restrict__ U, const In
 // Row gj of the state U, columns i0 - 2 .. i0 + 61 (ghost columns mapped), straight
 // into LDS at dst (NPLU planes of 64 values), past the vector registers, which are
 // what the stage kernel is short of.  Asynchronous: dma_wait() before its data is
-// read, dma_reads_done() before it may overwrite what was read.  A strip without
-// ghost columns whose rows all start on 16 bytes moves 16 bytes per lane, two planes
-// with one instruction (6 for the 12 planes of the Euler equations); the others take
-// 4 bytes per lane, which any width and column map allows (24 instructions).
+// read, dma_reads_done() before it may overwrite what was read.  A strip with
+// rows_aligned() moves 16 bytes per lane, two planes with one instruction (6 for the 12
+// planes of the Euler equations; pc: pair_column()); the others take 4 bytes per lane,
+// which any width and column map allows (24 instructions).
 using GlobalWord = const __attribute__((address_space(1))) unsigned;
 using LdsWord = __attribute__((address_space(3))) unsigned;
 
@@ -106,17 +106,24 @@ using LdsWord = __attribute__((address_space(3))) unsigned;
 __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void dma_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// whether every row of every plane of U starts on 16 bytes in this strip
+// whether the rows of every plane of U can be loaded 16 bytes a lane in this strip: rows
+// that start on 16 bytes, and ghost columns, if any, that are periodic images (i0 and nx
+// are even, so that a pair of columns has adjacent images)
 __device__ __forceinline__ bool rows_aligned(const double* U, const Inst& in, int i0) {
-  return i0 >= 2 && i0 + LANES - 2 <= in.nx && (((uintptr_t)U | (uintptr_t)(8 * (size_t)in.nx)) & 15) == 0;
+  return ((i0 >= 2 && i0 + LANES - 2 <= in.nx) || in.bcx == 0) &&
+         (((uintptr_t)U | (uintptr_t)(8 * (size_t)in.nx)) & 15) == 0;
+}
+// the column of this lane's pair of such a row
+__device__ __forceinline__ int pair_column(const Inst& in, int i0, int lane) {
+  return ghost(i0 - 2 + 2 * (lane & 31), in.nx, in.bcx);
 }
 
 template <int NPLU>
 __device__ __forceinline__ void dma_row(const double* __restrict__ U, const Inst& in, size_t plane, int i0, int gj,
-                                        int lane, double* dst, bool aligned) {
+                                        int lane, double* dst, bool aligned, int pc) {
   LdsWord* l = (LdsWord*)dst;
   if (aligned) {
-    const double* row = U + ((size_t)gj * in.nx + (i0 - 2)) + ((lane >> 5) * plane + 2 * (lane & 31));
+    const double* row = U + (size_t)gj * in.nx + ((lane >> 5) * plane + pc);
 #pragma unroll
     for (int p = 0; p < NPLU; p += 2) {
       if (p + 1 < NPLU || lane < 32)
@@ -138,8 +145,36 @@ __device__ __forceinline__ void dma_row(const double* __restrict__ U, const Inst
   }
 }
 
+// The same for a state whose moment planes lie moff elements after the places that U's
+// own would have (aligned: moff even too)
 template <int NPLU>
-__device__ __forceinline__ void store_row(Window<NPLU>& W, int slot, int lane, const double (&reg)[NPLU]) {
+__device__ __forceinline__ void dma_row_split(const double* __restrict__ U, long long moff, const Inst& in, int i0,
+                                              int gj, int lane, double* dst, bool aligned, int pc) {
+  LdsWord* l = (LdsWord*)dst;
+  const size_t plane = in.plane;
+  auto off = [&](int p) { return (long long)(p * plane) + (p % 3 == 0 ? 0 : moff); };
+  if (aligned) {
+    const double* row = U + (size_t)gj * in.nx + pc;
+#pragma unroll
+    for (int p = 0; p < NPLU; p += 2)
+      if (p + 1 < NPLU || lane < 32)
+        __builtin_amdgcn_global_load_lds((GlobalWord*)(row + (lane < 32 ? off(p) : off(p + 1))), l + p * 2 * LANES, 16,
+                                         0, 0);
+  } else {
+    const double* row = U + (size_t)gj * in.nx;
+    const int c0 = i0 - 2 + (lane >> 1);
+    GlobalWord* g0 = (GlobalWord*)(row + ghost(c0, in.nx, in.bcx)) + (lane & 1);
+    GlobalWord* g1 = (GlobalWord*)(row + ghost(c0 + LANES / 2, in.nx, in.bcx)) + (lane & 1);
+#pragma unroll
+    for (int p = 0; p < NPLU; ++p) {
+      __builtin_amdgcn_global_load_lds(g0 + 2 * off(p), l + p * 2 * LANES, 4, 0, 0);
+      __builtin_amdgcn_global_load_lds(g1 + 2 * off(p), l + p * 2 * LANES + LANES, 4, 0, 0);
+    }
+  }
+}
+
+template <int NPLU, int SLOTS>
+__device__ __forceinline__ void store_row(Window<NPLU, SLOTS>& W, int slot, int lane, const double (&reg)[NPLU]) {
 #pragma unroll
   for (int p = 0; p < NPLU; ++p) W.at(slot, p, lane) = reg[p];
 }
