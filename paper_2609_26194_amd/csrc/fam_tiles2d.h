@@ -137,6 +137,51 @@ __device__ __forceinline__ unsigned long long pp_cheap_test(const P& phys, const
   }
 }
 
+// Between the two, where many cells of a row fail the cheap test (a discontinuity along
+// the row): every lane evaluates its own cell's 32 points, and the cells at which density
+// and pressure stay clear of eps at all of them, by margins far above the rounding of
+// either evaluation, need no exact test (it would find factors of one).  Returns the
+// cells that do.  The margins: 1e-10 of the components' size, and a density of at least
+// a hundredth of the average, so that velocities stay within sqrt(200 E / rho).
+template <int K, int NCF, int MD, class P>
+__device__ __forceinline__ unsigned long long pp_points_test(const P& phys, const double (&cf)[P::NC][NCF],
+                                                             unsigned long long todo, double eps) {
+  constexpr int NC = P::NC;
+  if constexpr (NC != 4) {
+    return todo;
+  } else {
+    double size = fabs(cf[0][0]) + fabs(cf[3][0]);
+#pragma unroll
+    for (int l = 1; l < NCF; ++l)
+      size = fma(fabs(cf[0][l]) + fabs(cf[3][l]), leg(AX[l], 0.5) * leg(AY[l], 0.5), size);
+    const double lim = fma(1e-10, size, eps), ce = lim * rcp(phys.g1);
+    double rmin = cf[0][0], pmin = 1e300;
+    auto point = [&](const double (&u)[NC]) {
+      rmin = fmin(rmin, u[0]);
+      pmin = fmin(pmin, fma(u[0], u[3] - ce, -0.5 * fma(u[1], u[1], u[2] * u[2])));
+    };
+    // lines of points: the four volume nodes in y with the x-faces, then the y-faces
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      double up[3][NC], um[3][NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        double Q[MD + 1];
+        line_y<K>(cf[c], q < 4 ? q >> 1 : 2, (q & 1) ? -1.0 : 1.0, Q);
+#pragma unroll
+        for (int n = 0; n < (q < 4 ? 3 : 2); ++n) pair_x<MD>(Q, n, up[n][c], um[n][c]);
+      }
+#pragma unroll
+      for (int n = 0; n < (q < 4 ? 3 : 2); ++n) {
+        point(up[n]);
+        point(um[n]);
+      }
+      FAM_SCHED_FENCE();
+    }
+    return todo & __ballot(!(rmin > fmax(lim, 0.01 * cf[0][0]) && pmin > 0.0));
+  }
+}
+
 // The exact test, called by all 64 lanes of the wave for the few cells (near
 // discontinuities) that fail the cheap one: each half of the wave takes one of them
 // at a time, lane l evaluating flux point l mod 32 of it, so a pair of cells costs
@@ -237,6 +282,14 @@ __device__ __forceinline__ void pp_exact(const P& phys, double (&cf)[P::NC][NCF]
 // on a SIMD: a row's cycles depend on what the other wave does meanwhile, and the
 // segments of one launch took from 164 to 657 us.)
 constexpr float ROW_TEST = 1.8f, ROW_CELL = 0.15f;
+// From POINTS_MIN cells of a row on the point test comes first; it costs about as much
+// as the exact test of POINTS_CELLS cells.  Most rows with limiter work hold one or two
+// such cells, but a discontinuity along a row fills it, and the wave that has this row
+// ends last: four-quadrant data, us per pass without / with the test, 96x80 1944 / 993,
+// 256x256 2639 / 1733, 512x512 3998 / 3063, 2048x2048 15561 / 15030, six meshes of 64^2
+// to 128^2 2754 / 1247.  The double Mach reflection's and the characteristic variables'
+// kernels, whose registers are full, lose 1 % and 9 % on oblique shocks and go without.
+constexpr int POINTS_MIN = 6, POINTS_CELLS = 4;
 
 // ---------------------------------------------------------------------------
 // Registers and LDS of a stage wave.  What bounds the kernel is the issue of vector
@@ -641,7 +694,15 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
     if constexpr (PP) {
       // rare: 0.45 % of the cells, in 4.5 % of the rows of the four-quadrant problem
       double eps = 0.0;
-      const unsigned long long todo = pp_cheap_test<K, NCF>(phys, cf, bad, lane, eps);
+      unsigned long long todo = pp_cheap_test<K, NCF>(phys, cf, bad, lane, eps);
+      bool pointwise = false;
+      auto limit = [&]() __attribute__((always_inline)) {
+        if constexpr (!DMR && !CHAR) {
+          pointwise = __popcll(todo) >= POINTS_MIN;
+          if (pointwise) todo = pp_points_test<K, NCF, MD>(phys, cf, todo, eps);
+        }
+        if (todo) pp_exact<K, NCF, MD>(phys, cf, todo, eps, lane, S.nwork);
+      };
       if (__builtin_expect(todo != 0, 0)) {
         if constexpr (!RICH && K == 5) {
           // what the row carries waits in scratch memory meanwhile: kept in registers,
@@ -655,7 +716,7 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
             for (int m = 0; m < 3; ++m) park[5 * c + 2 + m] = Y[c][m];
           }
           asm volatile("" : : "v"((ScratchDouble*)park) : "memory");   // keeps it there
-          pp_exact<K, NCF, MD>(phys, cf, todo, eps, lane, S.nwork);
+          limit();
           asm volatile("" : : "v"((ScratchDouble*)park) : "memory");
 #pragma unroll
           for (int c = 0; c < NC; ++c) {
@@ -665,10 +726,10 @@ __device__ void stage_tile(const P& phys, const StageArgs& A, const Inst& in, in
             for (int m = 0; m < 3; ++m) Y[c][m] = park[5 * c + 2 + m];
           }
         } else {
-          pp_exact<K, NCF, MD>(phys, cf, todo, eps, lane, S.nwork);
+          limit();
         }
       }
-      finish_row(cf, r, __popcll(todo));
+      finish_row(cf, r, (pointwise ? POINTS_CELLS : 0) + __popcll(todo));
     } else {
       finish_row(cf, r, 0);
     }
