@@ -7,8 +7,8 @@ OE Type II, positivity limiter on (without it this data leaves the admissible
 set within 60-70 steps at k = 5; the limiter is the identity in every cell whose
 flux points are all admissible).  A step is the whole hot path: time step from the wave speeds, three
 SSP-RK3 stages (reconstruction, Lax-Friedrichs flux, volume quadrature,
-Shu-Osher update) and the OE pass.  Steps run through fam_run (replayed HIP
-graphs), inputs resident in HBM before the timed region.
+Shu-Osher update) and the OE pass.  Steps run through fam_run (long
+runs replay HIP graphs), inputs resident in HBM before the timed region.
 
 Prints one JSON line with the metric (cell-updates/s), a roofline object for the
 dominant kernel (the RK stage kernel, its launches timed with HIP events on the
@@ -333,7 +333,7 @@ def batched(steps):
     torch.cuda.synchronize()
     t_b = time.perf_counter() - t0
     bat.close()
-    # one context per instance, each advanced with its own graph-replayed fam_run
+    # one context per instance, each advanced with its own fam_run
     singles = [Fam(c) for c in cfgs]
     work = [s.clone() for s in states]
     for f, w in zip(singles, work):
@@ -452,7 +452,7 @@ def char_leg(so_n=4000, so_steps=2000, dmr_steps=1000):
     """Conservative against local characteristic variables for FAM5, the comparison of Table
     runtime-main Panel B: a Shu-Osher-type 1D run ([-5, 5], OE Type II, CFL 0.2) and the double
     Mach reflection (1440 x 480, limiter).  Each variant runs the same number of steps from the
-    same data (both tile heights autotuned in 2D); reported: ms per step (graph-replayed steps),
+    same data (both tile heights autotuned in 2D); reported: ms per step (fam_run),
     the RK stage launches (reconstruction, fluxes, quadrature: where the transform sits) and the
     OE launch of one step at the final state, and the ratios characteristic / conservative."""
     import dataclasses
@@ -527,8 +527,8 @@ def dmr_leg(t_final, cfl, nx=1440, ny=480):
                         f"CFL {cfl}, to t = {t:.4f}", "cfl": cfl, "steps": steps,
             "cell_updates_per_s": nx * ny * steps / elapsed,
             "ms_per_step": elapsed / steps * 1e3, "seconds": elapsed,
-            # standalone launches of one step (each stage launch re-cuts its segment list; inside the
-            # graph-replayed step that happens once), and the OE's share of them
+            # standalone launches of one step (each stage launch re-cuts its segment list; inside a
+            # step that happens once), and the OE's share of them
             "launch_ms": {"rk_stages": tot["stage"], "oe": tot["oe"]},
             "oe_fraction": tot["oe"] / (tot["stage"] + tot["oe"]),
             "autotuned_tile_heights": {"stage": tuned[0], "oe": tuned[1]}}
