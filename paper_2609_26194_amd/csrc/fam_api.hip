@@ -144,9 +144,10 @@ static fam_status init_steps(fam_ctx* c) {
     s.dim = c->dim;
   }
   HIP_TRY(hipMemcpy(c->st, h.data(), sizeof(StepState) * c->ninst, hipMemcpyHostToDevice));
-  // the wave-speed slots start at zero, as after a reset
-  const std::vector<double> none((size_t)fam::ALPHA_INST * c->ninst, 0.0);
-  HIP_TRY(hipMemcpy(c->alpha, none.data(), sizeof(double) * none.size(), hipMemcpyHostToDevice));
+  // the wave-speed slots start at zero, as after a reset (a kernel: a host copy of a large
+  // batch's slots could be gigabytes)
+  fam::launch_reset_steps(c->st, c->ninst, 0.0, 0.0, c->stream);
+  HIP_TRY(hipGetLastError());
   return FAM_OK;
 }
 
