@@ -187,7 +187,8 @@ fam_status fam_check(fam_ctx* ctx);
  * The context's stage buffers are overwritten, captured step graphs are
  * dropped, and the device flag is cleared.  choice (host, may be NULL, 2 ints)
  * receives (stage H, OE H) or (batch H, persistent blocks); stage H = 0 is the
- * segment list of a limiter-on context (fam_set_tiling).  Synchronous.
+ * segment list of a limiter-on context, and a height of 8 stands for the library's
+ * own one where that is lower (fam_set_tiling).  Synchronous.
  * FAM_ERR_ARG for a NULL context / state or reps < 1; 1D contexts: no-op. */
 fam_status fam_autotune(fam_ctx* ctx, const double* U, int reps, int* choice);
 
@@ -195,12 +196,13 @@ fam_status fam_autotune(fam_ctx* ctx, const double* U, int reps, int* choice);
  * that fam_autotune returned earlier): stage_H = strip-tile height of the RK
  * stage kernel, or 0 for the segment list of a limiter-on context (each strip
  * cut into segments of equal cost, recorded per row by the previous stage
- * launch; one round of waves); oe_H = tile height of the OE kernel.  On meshes
- * too small to fill the GPU with tiles of 8 rows a launch takes fewer rows than
- * the height set here or tuned.  Results are unchanged by the choice (bitwise).
- * Captured step graphs are dropped.
- * FAM_ERR_ARG for a NULL context, heights outside [8, ny] (or [1, ny] when ny <
- * 8) or stage_H = 0 without the limiter (or with more strips than wave slots);
+ * launch; one round of waves); oe_H = tile height of the OE kernel.  The least
+ * height, 8 (or ny when ny < 8), stands for the library's own one, which a new
+ * context launches with, on meshes too small to fill the GPU with tiles of 8
+ * rows, where that is lower; every other height is launched as set.  Results are
+ * unchanged by the choice (bitwise).  Captured step graphs are dropped.
+ * FAM_ERR_ARG for a NULL context, heights outside [8, ny] (or other than ny when
+ * ny < 8) or stage_H = 0 without the limiter (or with more strips than wave slots);
  * FAM_ERR_STATE for 1D or batched contexts.  Asynchronous. */
 fam_status fam_set_tiling(fam_ctx* ctx, int stage_H, int oe_H);
 

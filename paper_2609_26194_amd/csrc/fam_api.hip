@@ -255,10 +255,10 @@ extern "C" fam_status fam_init(const fam_config* cfg, void* hip_stream, fam_ctx*
   c->H = c->H_oe = 1;
   if (f.dim == 2) {
     const int ms = fam::stage_rows(f.nx, f.ny, f.k, c->nc, f.char_vars != 0), mo = fam::oe_rows(f.nx, f.ny, c->nc);
-    c->H = std::min(std::max(ms, 8), f.ny);
-    c->H_oe = std::min(std::max(mo, 8), f.ny);
-    c->H_most = ms < 8 ? ms : 0;
-    c->H_oe_most = mo < 8 ? mo : 0;
+    c->H = std::min(std::max(ms, LEAST_H), f.ny);
+    c->H_oe = std::min(std::max(mo, LEAST_H), f.ny);
+    c->H_model = ms < LEAST_H ? ms : 0;
+    c->H_oe_model = mo < LEAST_H ? mo : 0;
   }
   fam_status a = alloc_common(c);
   if (a == FAM_OK && f.dim == 2 && c->pp) {
@@ -283,11 +283,11 @@ extern "C" fam_status fam_init(const fam_config* cfg, void* hip_stream, fam_ctx*
 }
 
 // work list of a batch: (instance, i0, j0, H) strip tiles of height min(H, ny),
-// largest instances first (the persistent kernels take them round-robin); H is
-// Hmax, or the model's height of a batch so small that this is below 8
-static fam_status build_work_list(fam_ctx* c, int Hmax) {
+// largest instances first (the persistent kernels take them round-robin); H: a
+// tuned height, whose least, 8, stands for the model's where that is lower, or 0,
+// the default: 16, or that of the model where it is below 8
+static fam_status build_work_list(fam_ctx* c, int H_set) {
   const int n = c->ninst;
-  c->batch_H = Hmax;
   int most_rows = 1;
   for (const fam_config& f : c->cfg) most_rows = std::max(most_rows, f.ny);
   const int model = fam::model_rows(
@@ -298,7 +298,8 @@ static fam_status build_work_list(fam_ctx* c, int Hmax) {
         return tiles;
       },
       most_rows, fam::stage_waves(c->k, c->nc, false), c->nc == 1 ? 0.3 : 0.45);
-  Hmax = launch_H(Hmax, model < 8 ? model : 0);
+  c->batch_H = H_set > 0 ? H_set : model < LEAST_H ? LEAST_H : 16;
+  const int Hmax = launch_H(c->batch_H, model);
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
@@ -372,7 +373,7 @@ extern "C" fam_status fam_init_batched(const fam_config* per, int n, void* hip_s
     fam_destroy(c);
     return a;
   }
-  fam_status w = build_work_list(c, 16);
+  fam_status w = build_work_list(c, 0);
   if (w != FAM_OK) {
     fam_destroy(c);
     return w;
@@ -469,7 +470,7 @@ void enqueue_stage(fam_ctx* c, int s, int parity, const double* U0, const double
         fam::launch_partition(c->row_cost, c->row_pref, c->part_state, (f.nx + fam::STRIP - 1) / fam::STRIP, f.ny,
                             c->seg_budget, c->seg, c->nseg, c->stream);
     } else {
-      const int H = launch_H(c->H, c->H_most);
+      const int H = launch_H(c->H, c->H_model);
       if (H < c->H) A.tile_perm = nullptr;   // the order is that of the tiles of height H
       fam::launch_stage2d(c->k, c->sys, A, in, H, c->stream);
     }
@@ -501,7 +502,7 @@ void enqueue_oe(fam_ctx* c, int parity, const double* Un, double* Uout, const do
     if (c->dim == 1)
       fam::launch_oe1d(c->k, c->sys, A, in, c->stream);
     else
-      fam::launch_oe2d(c->k, c->sys, A, in, launch_H(c->H_oe, c->H_oe_most), c->stream);
+      fam::launch_oe2d(c->k, c->sys, A, in, launch_H(c->H_oe, c->H_oe_model), c->stream);
   } else {
     fam::launch_oe2d_batched(c->k, c->sys, A, c->d_insts[parity][3], c->d_work, c->nwork, c->pblocks, c->stream);
   }
@@ -594,7 +595,7 @@ extern "C" fam_status fam_oe(fam_ctx* c, const double* Un, double* Uout, const d
 extern "C" fam_status fam_set_tiling(fam_ctx* c, int stage_H, int oe_H) {
   if (!c) return FAM_ERR_ARG;
   if (c->dim != 2 || c->ninst != 1) return FAM_ERR_STATE;
-  const int ny = c->cfg[0].ny, hmin = std::min(8, ny);
+  const int ny = c->cfg[0].ny, hmin = std::min(LEAST_H, ny);
   if (oe_H < hmin || oe_H > ny) return FAM_ERR_ARG;
   if (stage_H == 0 ? c->seg_budget == 0 : (stage_H < hmin || stage_H > ny)) return FAM_ERR_ARG;
   destroy_graphs(c);
@@ -665,7 +666,8 @@ extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* c
   if (c->ninst == 1) {
     c->stage_list = false;
     const int ny = c->cfg[0].ny;
-    std::vector<int> cand = {8, 12, 16, 20, 24, 28, 32, 40, 48, 64};
+    // the first stands for the model's height where that is lower
+    std::vector<int> cand = {std::min(LEAST_H, ny), 12, 16, 20, 24, 28, 32, 40, 48, 64};
     // plus the heights whose tile count just fits m whole rounds of the chip's
     // wave slots (4 SIMDs per CU, one or two waves per SIMD)
     int dev = 0, cus = 0;
@@ -683,7 +685,7 @@ extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* c
     float best_s = 1e30f, best_o = 1e30f;
     int hs = c->H, ho = c->H_oe;
     for (int H : cand) {
-      if (H > ny && H != cand[0]) continue;
+      if (H > ny) continue;
       r = set_stage_H(c, H);
       if (r != FAM_OK) return r;
       c->H_oe = H;
@@ -721,7 +723,7 @@ extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* c
       choice[1] = ho;
     }
   } else {
-    const int candH[] = {8, 12, 16, 24, 32};
+    const int candH[] = {LEAST_H, 12, 16, 24, 32};   // the first: the model's where that is lower
     float best = 1e30f;
     int bh = c->batch_H, bp = c->pblocks;
     for (int H : candH) {

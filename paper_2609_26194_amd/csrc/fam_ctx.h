@@ -28,10 +28,10 @@ struct fam_ctx {
   int* flag = nullptr;
   double2* stats = nullptr;    // Type I: maxima per block
   double* partial = nullptr;   // Type I: sums per block
-  // rows per strip tile (single instance): the set or tuned heights, at least 8; the
-  // launches of a mesh so small that the model asks for fewer than 8 take the model's
+  // rows per strip tile (single instance), as set or tuned, at least 8 (or ny); the
+  // least of them stands for the model's height where that is lower (launch_H)
   int H = 32, H_oe = 32;       // stage and OE kernel
-  int H_most = 0, H_oe_most = 0;   // the model's height where below 8, else no bound (0)
+  int H_model = 0, H_oe_model = 0;   // the model's height where below 8, else 0
   // limiter on: order of the stage kernel's tiles (single instance) or work-list
   // items (batch), and the limiter work per tile / item of its last launch
   int* tile_perm = nullptr;
@@ -74,8 +74,9 @@ struct fam_ctx {
 
 fam_status validate_config(const fam_config& c);
 double default_gamma_k(int dim, int k);
-// rows per tile of a launch: H, or the model's `most` where that bounds it
-inline int launch_H(int H, int most) { return most > 0 && most < H ? most : H; }
+constexpr int LEAST_H = 8;   // least height that can be set or tuned
+// rows per tile of a launch at the set, tuned or default height H
+inline int launch_H(int H, int model) { return H <= LEAST_H && model > 0 && model < H ? model : H; }
 fam_status set_stage_H(fam_ctx* c, int H);
 fam::Inst inst_for(const fam_ctx* c, int i, int parity, int stage);
 fam_status reset_steps(fam_ctx* c, double t_final, double dt_fixed);
