@@ -530,9 +530,10 @@ void enqueue_step(fam_ctx* c, double* U, int parity, double dt_fixed, double t_f
 
 // 1D meshes that run in one workgroup: a whole chunk of steps is one launch
 static bool small_1d(const fam_ctx* c) { return c->dim == 1 && c->cfg[0].nx <= fam::run1d_max(c->nc); }
-static void enqueue_small_1d(fam_ctx* c, double* U, int nsteps, bool fresh, double dt_fixed, double t_final) {
-  fam::launch_run1d(c->k, c->sys, c->phys, U, make_inst(c, 0), c->st, c->flag, nsteps, fresh, dt_fixed, t_final, c->oe,
-                    c->gamma_k, c->stream);
+static void enqueue_small_1d(fam_ctx* c, double* U, int nsteps, int test, bool more, bool fresh, double dt_fixed,
+                             double t_final) {
+  fam::launch_run1d(c->k, c->sys, c->phys, U, make_inst(c, 0), c->st, c->flag, nsteps, test, more, fresh, dt_fixed,
+                    t_final, c->oe, c->gamma_k, c->stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -541,7 +542,7 @@ static void enqueue_small_1d(fam_ctx* c, double* U, int nsteps, bool fresh, doub
 extern "C" fam_status fam_step(fam_ctx* c, double* U, double dt_fixed, double* dt_used_dev) {
   if (!c || !U) return FAM_ERR_ARG;
   if (small_1d(c)) {
-    enqueue_small_1d(c, U, 1, true, dt_fixed, 0.0);
+    enqueue_small_1d(c, U, 1, 0, false, true, dt_fixed, 0.0);
   } else {
     fam_status r = reset_steps(c, 0.0, 0.0);
     if (r != FAM_OK) return r;
@@ -818,17 +819,14 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
   std::vector<StepState> h(c->ninst);
   int done_steps = 0;
   double tmin = 0.0;
-  // With an end time, the first chunk is two steps; each later chunk holds the
-  // steps still needed at the last step's dt (at most 64, rounded up to even), so
-  // few replays past the end time are no-ops.
-  // A small 1D mesh ends its run inside the kernel: a chunk (one launch) of up to
-  // 1024 steps keeps a launch within some milliseconds.
-  int next = small ? 1024 : tf > 0 ? 2 : limit;
+  // A small 1D mesh counts its chunks and ends its run inside the kernel: a launch of
+  // up to 1024 steps stays within some milliseconds.
+  int next = tf > 0 ? fam::RUN_FIRST : limit;
   while (launched < limit) {
-    const int chunk = std::min(limit - launched, next);
+    const int chunk = std::min(limit - launched, small ? 1024 : next);
     const int pairs = chunk / 2;
     if (small) {
-      enqueue_small_1d(c, U, chunk, launched == 0, dt_fixed, tf);
+      enqueue_small_1d(c, U, chunk, tf > 0 ? next : 0, chunk < limit - launched, launched == 0, dt_fixed, tf);
     } else {
       int p = 0;
       if (c->use_graph && pairs >= GRAPH_MIN_PAIRS) {
@@ -850,13 +848,17 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
     bool all_done = true;
     done_steps = 0;
     tmin = 1e300;
-    double need = 0.0;
+    if (tf > 0) next = fam::RUN_FIRST;
     for (auto& s : h) {
       const bool fin = (s.done != 0) || (tf > 0 && s.t >= tf);
       all_done &= fin;
       done_steps = std::max(done_steps, s.steps);
       tmin = std::min(tmin, s.t);
-      if (!fin && s.dt > 0.0) need = std::max(need, std::ceil((tf - s.t) / s.dt));
+      if (tf > 0 && !fin && s.dt > 0.0) next = std::max(next, fam::run_chunk(tf - s.t, s.dt));
+    }
+    if (small) {
+      if (tf > 0) launched = done_steps;   // it may have stopped before the chunk's end
+      else if (launched < limit && !all_done) continue;   // without one, tested once, at the end
     }
     int fl = 0;
     HIP_TRY(hipMemcpy(&fl, c->flag, sizeof(int), hipMemcpyDeviceToHost));
@@ -867,13 +869,8 @@ extern "C" fam_status fam_run(fam_ctx* c, double* U, double t_final, int max_ste
       HIP_TRY(hipMemcpy(c->flag, &z, sizeof(int), hipMemcpyHostToDevice));
       return FAM_ERR_NONPHYSICAL;
     }
-    if (tf > 0 && all_done) break;
-    if (small) continue;
-    if (chunk % 2) break;   // parity would break on another chunk; odd chunks only end a run
-    if (tf > 0) {
-      const int want = need > 62.0 ? 64 : std::max(2, (int)need);
-      next = want + (want & 1);
-    }
+    if ((tf > 0 || small) && all_done) break;
+    if (chunk % 2 && !small) break;   // parity would break on another chunk; odd chunks only end a run
   }
   if (steps_done) *steps_done = done_steps;
   if (t_done) *t_done = tmin;

@@ -198,7 +198,17 @@ void launch_stage1d(int k, int sys, const StageArgs& A, const Inst& in, hipStrea
 // side; the 1D Euler kernel needs more than the 128 registers a lane of 1024 may have
 __host__ __device__ constexpr int run1d_max(int nc) { return nc == 1 ? 1022 : 510; }
 void launch_run1d(int k, int sys, const PhysParams& pp, double* U, const Inst& in, StepState* st, int* flag,
-                  int nsteps, bool fresh, double dt_fixed, double t_final, int oe, double gamma_k, hipStream_t s);
+                  int nsteps, int test, bool more, bool fresh, double dt_fixed, double t_final, int oe,
+                  double gamma_k, hipStream_t s);
+// A run to an end time starts with RUN_FIRST steps; each later chunk holds the steps
+// still needed at the last step's dt, at most 64, rounded up to even, so that few steps
+// past the end time are no-ops.  After each chunk it tests for non-physical states.
+constexpr int RUN_FIRST = 2;
+__host__ __device__ inline int run_chunk(double t_left, double dt) {
+  const double need = ceil(t_left / dt);
+  const int want = need > 62.0 ? 64 : need > 2.0 ? (int)need : 2;
+  return want + (want & 1);
+}
 void launch_oe1d(int k, int sys, const OEArgs& A, const Inst& in, hipStream_t s);
 void launch_alpha1d(int sys, const PhysParams& pp, const double* U, const Inst& in, int* flag, hipStream_t s);
 

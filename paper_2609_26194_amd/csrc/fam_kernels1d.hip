@@ -370,10 +370,13 @@ __device__ __forceinline__ bool begin_step(const StepState& s, double ax, double
 // reduced in LDS.  As a sequence of launches such a step is five of 2 to 5 us, each
 // bound by its start and its one memory round trip.  Measured, us a step as
 // launches / here: Burgers 120 cells k=5 17.4 / 3.4, Euler 400 cells k=6 23.8 / 10.0.
+// A run to an end time tests for non-physical averages after the same steps as the
+// larger meshes' (first: after `test` steps, 0: not at all; then run_chunk) and stops
+// there; a launch that others follow (more) ends at such a step too.
 template <int K, class P, bool CHAR = false>
 __global__ void __launch_bounds__(run1d_max(P::NC) + 2) run1d_kernel(PhysParams pp, double* __restrict__ U, Inst in, StepState* st,
-                                                     int* flag, int nsteps, int fresh, double dt_fixed,
-                                                     double t_final, int oe, double gamma_k) {
+                                                     int* flag, int nsteps, int test, int more, int fresh,
+                                                     double dt_fixed, double t_final, int oe, double gamma_k) {
   constexpr int NC = P::NC;
   extern __shared__ double lds[];
   __shared__ double red[2][16];   // per wave: maxima of the speeds (and of Type I)
@@ -384,7 +387,7 @@ __global__ void __launch_bounds__(run1d_max(P::NC) + 2) run1d_kernel(PhysParams 
   const Tile1 S{lds, lds + NC * 2 * (T + 2), lds + NC * 3 * (T + 2), T + 2};
   double* sp = lds + NC * 4 * (T + 2);   // speeds of the cells of columns x
   const bool own = i >= 0 && i < n;
-  bool bad = false;
+  bool bad = test > 0 && *flag != 0;   // raised by an earlier call
 
   // value v of plane p (or of sp) in this lane's column and the ghost columns that mirror it
   auto put = [&](double* plane, double v) {
@@ -405,7 +408,7 @@ __global__ void __launch_bounds__(run1d_max(P::NC) + 2) run1d_kernel(PhysParams 
       double avg[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) avg[c] = u[c][0];
-      v = phys.speed(0, avg, bad);
+      v = fmax(0.0, phys.speed(0, avg, bad));   // a NaN raises the flag and is no maximum
     }
     put(sp, v);
     v = wave_max(v);
@@ -436,67 +439,77 @@ __global__ void __launch_bounds__(run1d_max(P::NC) + 2) run1d_kernel(PhysParams 
   double tm = s0.t, dt = fresh ? 0.0 : s0.dt;
   int steps = fresh ? 0 : s0.steps, done = fresh ? 0 : s0.done;
   const double eps1 = 1e-14;
+  int k = 0, next = test > 0 ? min(test, nsteps) : nsteps;   // the step before which the run is tested again
 #pragma unroll 1
-  for (int k = 0; k < nsteps; ++k) {
-    if (!begin_step(s0, alpha(), 0.0, dt_fixed, t_final, tm, dt, steps, done)) break;
-    const double dtx = dt / in.dx;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      u0[c][0] = u[c][0];
-      u0[c][1] = u[c][1];
-    }
+  for (;;) {
 #pragma unroll 1
-    for (int s = 0; s < 3; ++s) {
-      const double ca = s == 0 ? 0.0 : s == 1 ? 0.75 : 1.0 / 3.0;
-      double L[NC][2];
-      stage1_cell<K, P, CHAR>(phys, S, t, alpha(), dtx, L);
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) u[c][m] = s == 0 ? L[c][m] : fma(ca, u0[c][m] - L[c][m], L[c][m]);
-      __syncthreads();   // the maxima of this stage's input have been read
-#pragma unroll
-      for (int p = 0; p < NC * 2; ++p) put(S.u + p * S.W, u[p / 2][p % 2]);
-      speeds(u);
-      __syncthreads();
-    }
-    if (oe != 0) {
-      double D1[NC] = {}, e1[NC] = {};
-      if (oe == 1) {
-        // Type I: mean, then max |u - mean| and max |u|, over the block
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const double v = wave_sum(own ? u[c][0] : 0.0);
-          if ((t & 63) == 0) sum[wv] = v;
-          __syncthreads();
-          double mu = 0.0;
-          for (int w = 0; w < nw; ++w) mu += sum[w];
-          mu /= (double)n;
-          const double d = wave_max(own ? fabs(u[c][0] - mu) : 0.0), a = wave_max(own ? fabs(u[c][0]) : 0.0);
-          __syncthreads();
-          if ((t & 63) == 0) {
-            sum[wv] = d;
-            red[1][wv] = a;
-          }
-          __syncthreads();
-          double M = 0.0;
-          for (int w = 0; w < nw; ++w) {
-            D1[c] = fmax(D1[c], sum[w]);
-            M = fmax(M, red[1][w]);
-          }
-          e1[c] = eps1 * fmax(M, 1.0);
-          __syncthreads();
-        }
-      }
-      const double sig = oe1_sigma<K, P>(S, t, oe, gamma_k, D1, e1);
-      const double beta = fmax(fmax(sp[t], sp[t + 1]), sp[t + 2]);
-      const double delta = exp(-beta * dt * sig / in.dx);
+    for (; k < next; ++k) {
+      if (!begin_step(s0, alpha(), 0.0, dt_fixed, t_final, tm, dt, steps, done)) break;
+      const double dtx = dt / in.dx;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        u[c][1] = delta * u[c][1];
-        put(S.u + (c * 2 + 1) * S.W, u[c][1]);
+        u0[c][0] = u[c][0];
+        u0[c][1] = u[c][1];
       }
-      __syncthreads();
+#pragma unroll 1
+      for (int s = 0; s < 3; ++s) {
+        const double ca = s == 0 ? 0.0 : s == 1 ? 0.75 : 1.0 / 3.0;
+        double L[NC][2];
+        stage1_cell<K, P, CHAR>(phys, S, t, alpha(), dtx, L);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int m = 0; m < 2; ++m) u[c][m] = s == 0 ? L[c][m] : fma(ca, u0[c][m] - L[c][m], L[c][m]);
+        __syncthreads();   // the maxima of this stage's input have been read
+#pragma unroll
+        for (int p = 0; p < NC * 2; ++p) put(S.u + p * S.W, u[p / 2][p % 2]);
+        speeds(u);
+        __syncthreads();
+      }
+      if (oe != 0) {
+        double D1[NC] = {}, e1[NC] = {};
+        if (oe == 1) {
+          // Type I: mean, then max |u - mean| and max |u|, over the block
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const double v = wave_sum(own ? u[c][0] : 0.0);
+            if ((t & 63) == 0) sum[wv] = v;
+            __syncthreads();
+            double mu = 0.0;
+            for (int w = 0; w < nw; ++w) mu += sum[w];
+            mu /= (double)n;
+            const double d = wave_max(own ? fabs(u[c][0] - mu) : 0.0), a = wave_max(own ? fabs(u[c][0]) : 0.0);
+            __syncthreads();
+            if ((t & 63) == 0) {
+              sum[wv] = d;
+              red[1][wv] = a;
+            }
+            __syncthreads();
+            double M = 0.0;
+            for (int w = 0; w < nw; ++w) {
+              D1[c] = fmax(D1[c], sum[w]);
+              M = fmax(M, red[1][w]);
+            }
+            e1[c] = eps1 * fmax(M, 1.0);
+            __syncthreads();
+          }
+        }
+        const double sig = oe1_sigma<K, P>(S, t, oe, gamma_k, D1, e1);
+        const double beta = fmax(fmax(sp[t], sp[t + 1]), sp[t + 2]);
+        const double delta = exp(-beta * dt * sig / in.dx);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          u[c][1] = delta * u[c][1];
+          put(S.u + (c * 2 + 1) * S.W, u[c][1]);
+        }
+        __syncthreads();
+      }
+    }
+    if (done || k == nsteps || __syncthreads_or(bad)) break;
+    next += run_chunk(t_final - tm, dt);
+    if (next > nsteps) {
+      if (more) break;
+      next = nsteps;
     }
   }
 #pragma unroll
@@ -601,18 +614,19 @@ void launch_stage1d(int k, int sys, const StageArgs& A, const Inst& in, hipStrea
 }
 // steps of a mesh that run1d_fits; fresh: the first of a run (its books start anew)
 void launch_run1d(int k, int sys, const PhysParams& pp, double* U, const Inst& in, StepState* st, int* flag,
-                  int nsteps, bool fresh, double dt_fixed, double t_final, int oe, double gamma_k, hipStream_t s) {
+                  int nsteps, int test, bool more, bool fresh, double dt_fixed, double t_final, int oe,
+                  double gamma_k, hipStream_t s) {
   const int T = (in.nx + 2 + 63) / 64 * 64;
   const int nc = sys == 2 ? 3 : 1;
   const size_t lds = sizeof(double) * (nc * 4 + 1) * (T + 2);
   if (in.charv && sys == 2 && k == 5) {
     hipLaunchKernelGGL((run1d_kernel<5, Euler<1>, true>), dim3(1), dim3(T), lds, s, pp, U, in, st, flag, nsteps,
-                       (int)fresh, dt_fixed, t_final, oe, gamma_k);
+                       test, (int)more, (int)fresh, dt_fixed, t_final, oe, gamma_k);
     return;
   }
   FAM_DISPATCH_P1(sys, FAM_DISPATCH_K1(k, hipLaunchKernelGGL((run1d_kernel<KK, PP>), dim3(1), dim3(T), lds, s, pp, U, in,
-                                                            st, flag, nsteps, (int)fresh, dt_fixed, t_final, oe,
-                                                            gamma_k)));
+                                                            st, flag, nsteps, test, (int)more, (int)fresh, dt_fixed,
+                                                            t_final, oe, gamma_k)));
 }
 void launch_oe1d(int k, int sys, const OEArgs& A, const Inst& in, hipStream_t s) {
   const dim3 grid((in.nx + OUT1 - 1) / OUT1);

@@ -161,7 +161,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   const fam::PhysParams phys{f.gamma, f.ax, f.ay};
   if (dim == 1 && f.nx <= fam::run1d_max(nc)) {
     // one workgroup, one launch, as in fam_step
-    fam::launch_run1d(f.k, f.system, phys, U, in, st, flag, 1, false, dt_fixed, 0.0, f.oe,
+    fam::launch_run1d(f.k, f.system, phys, U, in, st, flag, 1, 0, false, false, dt_fixed, 0.0, f.oe,
                       f.oe_gamma_k > 0 ? f.oe_gamma_k : default_gamma_k(dim, f.k), s);
     if (dt_used_dev &&
         hipMemcpyAsync(dt_used_dev, &st->dt, sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess)
