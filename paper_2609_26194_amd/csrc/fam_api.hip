@@ -98,7 +98,10 @@ static Inst make_inst(const fam_ctx* c, int i) {
 Inst inst_for(const fam_ctx* c, int i, int parity, int stage) {
   Inst in = make_inst(c, i);
   StepState* s = c->st + i;
-  auto set = [&](int p, int q) { return c->alpha + (size_t)i * fam::ALPHA_INST + (3 * p + q) * fam::ALPHA_SET; };
+  const bool spread = c->ninst == 1;
+  auto set = [&](int p, int q) {
+    return c->alpha + i * fam::alpha_inst(spread) + fam::alpha_set(spread, 3 * p + q);
+  };
   if (stage < 3) {
     in.alpha_in = set(parity, stage);
     in.alpha_out = stage < 2 ? set(parity, stage + 1) : set(1 - parity, 0);
@@ -120,7 +123,7 @@ static fam_status alloc_common(fam_ctx* c) {
   if (hipMalloc(&c->W1, bytes) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->W2, bytes) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->st, sizeof(StepState) * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
-  if (hipMalloc(&c->alpha, sizeof(double) * fam::ALPHA_INST * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
+  if (hipMalloc(&c->alpha, sizeof(double) * fam::alpha_inst(c->ninst == 1) * c->ninst) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->flag, sizeof(int) * 4) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->stats, sizeof(double2) * 4 * fam::TYPE1_BLOCKS) != hipSuccess) return FAM_ERR_NOMEM;
   if (hipMalloc(&c->partial, sizeof(double) * 4 * fam::TYPE1_BLOCKS) != hipSuccess) return FAM_ERR_NOMEM;
@@ -136,7 +139,7 @@ static fam_status init_steps(fam_ctx* c) {
     StepState& s = h[i];
     std::memset(&s, 0, sizeof(s));
     const fam_config& f = c->cfg[i];
-    s.alpha = c->alpha + (size_t)i * fam::ALPHA_INST;
+    s.alpha = c->alpha + i * fam::alpha_inst(c->ninst == 1);
     s.cfl = f.cfl;
     const double e = f.dt_rule == 1 ? f.k / 3.0 : 1.0;
     s.hx = std::pow((f.x1 - f.x0) / f.nx, e);
@@ -144,8 +147,7 @@ static fam_status init_steps(fam_ctx* c) {
     s.dim = c->dim;
   }
   HIP_TRY(hipMemcpy(c->st, h.data(), sizeof(StepState) * c->ninst, hipMemcpyHostToDevice));
-  // the wave-speed slots start at zero, as after a reset (a kernel: a host copy of a large
-  // batch's slots could be gigabytes)
+  // the wave-speed slots start at zero, as after a reset
   fam::launch_reset_steps(c->st, c->ninst, 0.0, 0.0, c->stream);
   HIP_TRY(hipGetLastError());
   return FAM_OK;

@@ -24,7 +24,7 @@ struct fam_ctx {
   double* W1 = nullptr;
   double* W2 = nullptr;
   fam::StepState* st = nullptr;
-  double* alpha = nullptr;     // wave-speed slots, ALPHA_INST per instance
+  double* alpha = nullptr;     // wave-speed slots, alpha_inst per instance
   int* flag = nullptr;
   double2* stats = nullptr;    // Type I: maxima per block
   double* partial = nullptr;   // Type I: sums per block

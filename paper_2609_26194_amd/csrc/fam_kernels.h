@@ -70,8 +70,8 @@ struct Inst {
   size_t offset;           // start of the instance in a batched state (doubles)
   double dx, dy;
   int bcx, bcy;            // 0 periodic, 1 transmissive
-  const double* alpha_in;  // ALPHA_SET: wave speeds of the stage input state
-  double* alpha_out;       // ALPHA_SET: max-accumulators for the stage output state
+  const double* alpha_in;  // a set: wave speeds of the stage input state
+  double* alpha_out;       // a set: max-accumulators for the stage output state
   const double* dt;        // time step of the current step
   const int* done;         // instance finished (fam_run), may be null
   // double Mach reflection boundaries (dmr != 0): the boundary time of a launch is
@@ -140,11 +140,20 @@ struct OEArgs {
 constexpr int ALPHA_SLOTS = 32;
 constexpr int ALPHA_STRIDE = 16;                          // doubles: 128 B
 constexpr int ALPHA_SET = ALPHA_SLOTS * ALPHA_STRIDE;     // one maximum (x, y)
-constexpr int ALPHA_INST = 6 * ALPHA_SET;                 // of an instance: [parity][stage input 0..2]
+// Batches keep one slot per set: their atomics go to as many lines as there are
+// instances, and with slots a small instance would hold as much memory for them as for
+// its state (16x16 Euler: 24 KB).  An instance has two lines: a launch reads one set and
+// accumulates the next, and reads of the line that the atomics go to wait for them (two
+// meshes of 2000^2, a step 2960 us with all sets in one line, 2470 with two).
+// Offset of set 3 parity + (stage input 0..2) of an instance, and an instance's doubles
+__host__ __device__ constexpr size_t alpha_set(bool spread, int set) {
+  return spread ? (size_t)set * ALPHA_SET : (set % 2) * ALPHA_STRIDE + (set / 2) * 2;
+}
+__host__ __device__ constexpr size_t alpha_inst(bool spread) { return spread ? 6 * ALPHA_SET : 2 * ALPHA_STRIDE; }
 
 // per-instance step bookkeeping (device)
 struct StepState {
-  double* alpha;           // [parity][stage input 0..2][ALPHA_SET]
+  double* alpha;           // wave-speed maxima: alpha_inst doubles
   double dt;               // time step of the current step
   double t;                // time reached: the context clock (0 at set-up, advanced by every step)
   double t_final;          // <= 0: none

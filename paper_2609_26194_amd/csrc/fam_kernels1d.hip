@@ -537,18 +537,32 @@ __device__ __forceinline__ void alpha_clear(double* s0, int n) {
     *reinterpret_cast<double2*>(s0 + (size_t)k * ALPHA_STRIDE) = make_double2(0.0, 0.0);
 }
 
-// one wave per instance: it reads and clears the slots, lane 0 keeps the books
-__global__ void __launch_bounds__(64) step_begin_kernel(StepState* st, int parity, double dt_fixed, double t_final) {
-  StepState& s = st[blockIdx.x];
-  const int q = parity, o = 1 - parity;
+// A single mesh: one wave, which reads and clears the slots; lane 0 keeps the books.
+// A batch (SPREAD = false): a lane per instance.
+template <bool SPREAD>
+__global__ void __launch_bounds__(64) step_begin_kernel(StepState* st, int ninst, int parity, double dt_fixed,
+                                                        double t_final) {
+  const int id = SPREAD ? 0 : blockIdx.x * 64 + threadIdx.x;
+  if (id >= ninst) return;
+  StepState& s = st[id];
+  // sets 1, 2 of this parity and 0 of the other are accumulated by this step's stages
+  double* in = s.alpha + alpha_set(SPREAD, 3 * parity);
+  double* out[3] = {s.alpha + alpha_set(SPREAD, 3 * parity + 1), s.alpha + alpha_set(SPREAD, 3 * parity + 2),
+                    s.alpha + alpha_set(SPREAD, 3 * (1 - parity))};
   double ax, ay;
-  alpha_max(alpha_load(s.alpha + 3 * q * ALPHA_SET), ax, ay);
-  alpha_clear(s.alpha + (3 * q + 1) * ALPHA_SET, 2 * ALPHA_SLOTS);
-  alpha_clear(s.alpha + 3 * o * ALPHA_SET, ALPHA_SLOTS);
-  if (threadIdx.x != 0) return;
-  // slot 0 holds the maximum for the stage kernels that read no other
-  s.alpha[3 * q * ALPHA_SET] = ax;
-  s.alpha[3 * q * ALPHA_SET + 1] = ay;
+  if constexpr (SPREAD) {
+    alpha_max(alpha_load(in), ax, ay);
+    alpha_clear(out[0], 2 * ALPHA_SLOTS);
+    alpha_clear(out[2], ALPHA_SLOTS);
+    if (threadIdx.x != 0) return;
+    // slot 0 holds the maximum for the stage kernels that read no other
+    in[0] = ax;
+    in[1] = ay;
+  } else {
+    ax = in[0];
+    ay = in[1];
+    for (double* o : out) o[0] = o[1] = 0.0;
+  }
   double t = s.t, dt;
   int steps = s.steps, done = s.done;
   if (begin_step(s, ax, ay, dt_fixed, t_final, t, dt, steps, done)) {
@@ -559,19 +573,30 @@ __global__ void __launch_bounds__(64) step_begin_kernel(StepState* st, int parit
   s.done = done;
 }
 
-__global__ void __launch_bounds__(64) reset_steps_kernel(StepState* st, double t_final, double dt_fixed) {
-  StepState& s = st[blockIdx.x];
-  alpha_clear(s.alpha, 6 * ALPHA_SLOTS);
-  if (threadIdx.x != 0) return;
+template <bool SPREAD>
+__global__ void __launch_bounds__(64) reset_steps_kernel(StepState* st, int ninst, double t_final, double dt_fixed) {
+  const int id = SPREAD ? 0 : blockIdx.x * 64 + threadIdx.x;
+  if (id >= ninst) return;
+  StepState& s = st[id];
+  if constexpr (SPREAD) {
+    alpha_clear(s.alpha, 6 * ALPHA_SLOTS);
+    if (threadIdx.x != 0) return;
+  } else {
+    for (size_t k = 0; k < alpha_inst(false); ++k) s.alpha[k] = 0.0;
+  }
   s.dt = 0.0;
   s.t_final = t_final;
   s.dt_fixed = dt_fixed;
-  s.done = 0;
   s.steps = 0;
+  s.done = 0;
 }
 
 void launch_reset_steps(StepState* st, int ninst, double t_final, double dt_fixed, hipStream_t s) {
-  hipLaunchKernelGGL(reset_steps_kernel, dim3(ninst), dim3(64), 0, s, st, t_final, dt_fixed);
+  if (ninst == 1)
+    hipLaunchKernelGGL(reset_steps_kernel<true>, dim3(1), dim3(64), 0, s, st, 1, t_final, dt_fixed);
+  else
+    hipLaunchKernelGGL(reset_steps_kernel<false>, dim3((ninst + 63) / 64), dim3(64), 0, s, st, ninst, t_final,
+                       dt_fixed);
 }
 
 // the context clock: every instance's time set to t (a kernel, not a memset, so a
@@ -586,7 +611,11 @@ void launch_set_time(StepState* st, int ninst, double t, hipStream_t s) {
 }
 
 void launch_step_begin(StepState* st, int ninst, int parity, double dt_fixed, double t_final, hipStream_t s) {
-  hipLaunchKernelGGL(step_begin_kernel, dim3(ninst), dim3(64), 0, s, st, parity, dt_fixed, t_final);
+  if (ninst == 1)
+    hipLaunchKernelGGL(step_begin_kernel<true>, dim3(1), dim3(64), 0, s, st, 1, parity, dt_fixed, t_final);
+  else
+    hipLaunchKernelGGL(step_begin_kernel<false>, dim3((ninst + 63) / 64), dim3(64), 0, s, st, ninst, parity, dt_fixed,
+                       t_final);
 }
 
 #define FAM_DISPATCH_K1(K_, BODY)                    \

@@ -278,8 +278,12 @@ __global__ void FAM_OE_ATTR oe2d_kernel(OEArgs A, Inst in, int H) {
 // ---------------------------------------------------------------------------
 // reductions over cell averages
 // ---------------------------------------------------------------------------
-// alpha_out[inst] = max over cells of the spectral radii at the averages
-template <class P>
+// alpha_out[inst] = max over cells of the spectral radii at the averages.  SPREAD (one
+// mesh): every wave adds to one of the slots; a batch: every block to the one there is,
+// which takes 24 ns a block, so a mesh has up to 256 blocks (a single step of 40 meshes
+// of 64^2 to 512^2, us with 256 / 512 / 1024: 1155 / 1170 / 1198; two of 2000^2 2461 /
+// 2459 / 2475).
+template <class P, bool SPREAD>
 __global__ void __launch_bounds__(256) alpha2d_kernel(PhysParams pp, const double* __restrict__ U,
                                                       const Inst* __restrict__ insts, int ninst, int* flag) {
   const P phys = make_phys<P>(pp);
@@ -288,6 +292,7 @@ __global__ void __launch_bounds__(256) alpha2d_kernel(PhysParams pp, const doubl
   for (int inst = blockIdx.y; inst < ninst; inst += gridDim.y) {
     const Inst in = insts[inst];
     const size_t n = (size_t)in.nx * in.ny;
+    if ((size_t)blockIdx.x * blockDim.x >= n) continue;
     double mx = 0.0, my = 0.0;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n;
          idx += (size_t)gridDim.x * blockDim.x) {
@@ -299,10 +304,21 @@ __global__ void __launch_bounds__(256) alpha2d_kernel(PhysParams pp, const doubl
     }
     mx = wave_max(mx);
     my = wave_max(my);
-    if ((threadIdx.x & 63) == 0) {
-      double* slot = alpha_slot(in.alpha_out, blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64);
-      atomic_max_nonneg(&slot[0], mx);
-      atomic_max_nonneg(&slot[1], my);
+    if constexpr (SPREAD) {
+      if ((threadIdx.x & 63) == 0) {
+        double* slot = alpha_slot(in.alpha_out, blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64);
+        atomic_max_nonneg(&slot[0], mx);
+        atomic_max_nonneg(&slot[1], my);
+      }
+    } else {
+      __shared__ double2 red[4];
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_double2(mx, my);
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        atomic_max_nonneg(&in.alpha_out[0], fmax(fmax(red[0].x, red[1].x), fmax(red[2].x, red[3].x)));
+        atomic_max_nonneg(&in.alpha_out[1], fmax(fmax(red[0].y, red[1].y), fmax(red[2].y, red[3].y)));
+      }
+      __syncthreads();
     }
   }
   if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
@@ -471,9 +487,13 @@ void launch_oe2d(int k, int sys, const OEArgs& A, const Inst& in, int H, hipStre
 }
 void launch_alpha2d(int sys, const PhysParams& pp, const double* U, const Inst* insts, int ninst,
                     size_t max_cells, int* flag, hipStream_t s) {
-  int bx = (int)std::min<size_t>((max_cells + 255) / 256, 1024);
-  dim3 grid(bx < 1 ? 1 : bx, std::min(ninst, 65535));
-  FAM_DISPATCH_P(sys, hipLaunchKernelGGL((alpha2d_kernel<PP>), grid, dim3(256), 0, s, pp, U, insts, ninst, flag));
+  const int bx = (int)std::min<size_t>((max_cells + 255) / 256, ninst == 1 ? 1024 : 256);
+  const dim3 grid(bx < 1 ? 1 : bx, std::min(ninst, 65535));
+  if (ninst == 1) {
+    FAM_DISPATCH_P(sys, hipLaunchKernelGGL((alpha2d_kernel<PP, true>), grid, dim3(256), 0, s, pp, U, insts, ninst, flag));
+  } else {
+    FAM_DISPATCH_P(sys, hipLaunchKernelGGL((alpha2d_kernel<PP, false>), grid, dim3(256), 0, s, pp, U, insts, ninst, flag));
+  }
 }
 void launch_type1_stats(const double* U, const Inst& in, int nc, int nmom, double* partial, double2* stats,
                         hipStream_t s) {

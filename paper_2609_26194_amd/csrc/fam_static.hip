@@ -39,7 +39,7 @@ constexpr size_t OFF_PARTIAL = 1536;      // Type I: sums per block
 constexpr size_t OFF_TILES = 10240;       // limiter: tile order (ntiles + 1) and work (ntiles) ints
 constexpr size_t TILE_BYTES = 128 * 1024;
 constexpr size_t OFF_ALPHA = OFF_TILES + TILE_BYTES;   // wave-speed slots
-constexpr size_t OFF_STATS = OFF_ALPHA + fam::ALPHA_INST * sizeof(double);   // Type I: maxima per block
+constexpr size_t OFF_STATS = OFF_ALPHA + fam::alpha_inst(true) * sizeof(double);   // Type I: maxima per block
 constexpr size_t OFF_W = 256 * 1024;      // W1, W2: two stage states
 static_assert(sizeof(StepState) <= OFF_FLAG - OFF_ST, "StepState slot");
 static_assert(sizeof(Inst) <= OFF_PARTIAL - OFF_AINST, "Inst slot");
@@ -144,7 +144,7 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   in.t_end = &st->t;
   StepState s0{};
   s0.alpha = reinterpret_cast<double*>(base + OFF_ALPHA);
-  auto alpha = [&](int p, int q) { return s0.alpha + (3 * p + q) * fam::ALPHA_SET; };
+  auto alpha = [&](int p, int q) { return s0.alpha + fam::alpha_set(true, 3 * p + q); };
   s0.cfl = f.cfl;
   const double e = f.dt_rule == 1 ? f.k / 3.0 : 1.0;
   s0.hx = std::pow(in.dx, e);
