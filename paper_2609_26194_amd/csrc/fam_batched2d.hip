@@ -64,9 +64,9 @@ static void launch_stage2d_b(const StageArgs& A, const Inst* insts, const int4* 
   if (A.pp) {
     hipLaunchKernelGGL((stage2d_batched_kernel<K, P, true>), dim3(nblocks), dim3(LANES), 0, s, A, insts, work,
                        nwork);
-    // (renewed after stage 0 only, a step of 40 meshes takes 2 % longer, though a renewal
-    // is 6 us); items that all start at once need no order
-    if (nwork > SIMDS * stage_waves(K, P::NC, false)) launch_tile_order(A.tile_work, const_cast<int*>(A.tile_perm), nwork, s);
+    // (renewed after stage 0 only, a step of 40 meshes takes 2 % longer, though a renewal is 6 us)
+    if (!starts_at_once(nblocks, nwork, stage_waves(K, P::NC, false)))
+      launch_tile_order(A.tile_work, const_cast<int*>(A.tile_perm), nwork, s);
   } else
     hipLaunchKernelGGL((stage2d_batched_kernel<K, P, false>), dim3(nblocks), dim3(LANES), 0, s, A, insts, work,
                        nwork);

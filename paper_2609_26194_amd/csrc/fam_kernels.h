@@ -18,6 +18,14 @@ __host__ __device__ constexpr int stage_waves(int k, int nc, bool charv) {
 
 constexpr int SIMDS = 1024;   // 256 CUs x 4
 
+// Whether the tiles (or work-list items) of a launch all start at once: a workgroup of
+// one wave each, and a wave slot for every workgroup.  Then their order does not matter
+// and is not renewed (6 us; six meshes 5 % faster).  A grid of fewer workgroups than
+// items takes them in turns, in that order.
+inline bool starts_at_once(int nblocks, int nitems, int waves) {
+  return nblocks == nitems && nitems <= SIMDS * waves;
+}
+
 // Rows per strip tile from a model of a launch of tiles(H) waves.  A tile of H rows
 // costs H + 2 row times (it also reconstructs a ring row on either side); w waves
 // on a SIMD take 1 + share (w - 1) times as long as one, up to `waves` of them,

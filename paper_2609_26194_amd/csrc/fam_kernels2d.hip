@@ -395,8 +395,7 @@ static void launch_stage2d_d(StageArgs A, const Inst& in, int H, hipStream_t s) 
   dim3 grid((in.nx + STRIP - 1) / STRIP, (in.ny + H - 1) / H);
   if (A.pp) {
     const int ntiles = grid.x * grid.y;
-    // up to one tile per wave slot of the chip every tile starts at once: no order
-    if (ntiles <= SIMDS * stage_waves(K, P::NC, CHAR)) A.tile_perm = nullptr;
+    if (starts_at_once(ntiles, ntiles, stage_waves(K, P::NC, CHAR))) A.tile_perm = nullptr;
     hipLaunchKernelGGL((stage2d_kernel<K, P, true, DMR, CHAR>), dim3(ntiles), dim3(LANES), 0, s, A, in, H);
     if (A.tile_perm) launch_tile_order(A.tile_work, const_cast<int*>(A.tile_perm), ntiles, s);
   } else {
