@@ -98,13 +98,14 @@ extern "C" fam_status fam_step_static(const fam_config* cfg, void* hip_stream, d
   const size_t cells = (size_t)f.nx * f.ny;
   const size_t len = cells * nc * nmom;
   if (len > LEN_LIMIT) return FAM_ERR_SIZE;
-  // launch shapes of a fresh context; the limiter's tile order where its slot holds it
+  // launch shapes of a fresh context; the limiter's tile order for the meshes whose tiles
+  // do not all start at once (wide and flat ones at one wave per SIMD, from 20461 x 15 on: up to 2905 tiles)
   const int strips = (f.nx + fam::STRIP - 1) / fam::STRIP;
   const int H = dim == 2 ? fam::stage_rows(f.nx, f.ny, f.k, nc, f.char_vars != 0) : 1;
   const int H_oe = dim == 2 ? fam::oe_rows(f.nx, f.ny, nc) : 1;
   const int ntiles = dim == 2 ? strips * ((f.ny + H - 1) / H) : 0;
-  const bool order = f.pp && (size_t)(2 * ntiles + 1) * sizeof(int) <= TILE_BYTES;
-  if (f.pp && (2 * (size_t)strips * ((f.ny + 31) / 32) + 1) * sizeof(int) > TILE_BYTES) return FAM_ERR_SIZE;
+  const bool order = f.pp && !fam::starts_at_once(ntiles, ntiles, fam::stage_waves(f.k, nc, f.char_vars != 0)) &&
+                     (size_t)(2 * ntiles + 1) * sizeof(int) <= TILE_BYTES;
 
   char* base = nullptr;
   fam_status r = scratch_ptr(&base);
