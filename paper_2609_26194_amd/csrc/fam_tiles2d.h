@@ -295,10 +295,12 @@ constexpr int POINTS_MIN = 6, POINTS_CELLS = 4;
 // Registers and LDS of a stage wave.  What bounds the kernel is the issue of vector
 // instructions (about 2150 per row of 64 cells at k = 5, 1670 of them FP64), so it
 // is written for few of them and for a second wave on the SIMD to fill the gaps:
-// two waves have 256 registers and 20 KB of LDS each.  k = 3..5 fit without spilling
-// (k = 5: 120 registers of coefficients, 40 carried from row to row), because rows
-// go to LDS past the registers and each line's points are used as soon as they are
-// evaluated.  A single spill in the row's second half is expensive: its reload waits
+// two waves have 256 registers and 20 KB of LDS each.  The rows of k = 3..5 fit without
+// spilling (k = 5: 120 registers of coefficients, 40 carried from row to row), because
+// rows go to LDS past the registers and each line's points are used as soon as they are
+// evaluated.  (The limiter's point test, which few rows take, spills within itself: one
+// value on a single mesh at k = 5, five and seven in a batch at k = 4 and 5; a test
+// watches the counts.)  A single spill in the row's second half is expensive: its reload waits
 // for the row prefetch issued before it (33 of them made the kernel 1.5x slower).
 // k = 6 (168 registers of coefficients) and the characteristic variables run one
 // wave per SIMD and use its 40 KB of LDS instead: what a row hands to the next (20
