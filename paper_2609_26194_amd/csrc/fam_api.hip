@@ -631,8 +631,9 @@ extern "C" fam_status fam_dbg_oe_factors(fam_ctx* c, const double* Un, const dou
 // ---------------------------------------------------------------------------
 // autotuner: times the candidate launch shapes on the caller's state and keeps
 // the fastest.  Single 2D instance: the strip-tile height of the stage kernel
-// and of the OE kernel (the tile count against the 1024 wave slots of the chip
-// sets the tail of the last round of waves; shorter tiles add ring rows).
+// and of the OE kernel (the tile count against the wave slots of the chip, 1024 or
+// 2048 with two waves per SIMD, sets the tail of the last round of waves; shorter
+// tiles add ring rows).
 // Batch: the tile height of the work list and the persistent grid size.
 // ---------------------------------------------------------------------------
 static fam_status time_launches(fam_ctx* c, int reps, const std::function<void()>& body, float* ms) {
@@ -654,6 +655,12 @@ static fam_status time_launches(fam_ctx* c, int reps, const std::function<void()
   if (r == FAM_OK && hipGetLastError() != hipSuccess) r = FAM_ERR_DEVICE;
   return r;
 }
+
+// The heights are tried in ascending order up to the first whose launch takes this many
+// times the best's: from there on, where the rows' latency decides, a launch's time grows
+// with its rows (us a stage launch, k = 5: 128x128 with the least height, one row, 13,
+// with 12 rows 60, 64 rows 286; 2048x2048 between 321 and 490 from 8 to 64 rows)
+constexpr float TUNE_STOP = 2.0f;
 
 extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* choice) {
   if (!c || !U || reps < 1) return FAM_ERR_ARG;
@@ -685,21 +692,27 @@ extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* c
         const int H = (ny + per - 1) / per;
         if (H >= 8 && H <= ny && std::find(cand.begin(), cand.end(), H) == cand.end()) cand.push_back(H);
       }
+    std::sort(cand.begin(), cand.end());
     float best_s = 1e30f, best_o = 1e30f;
     int hs = c->H, ho = c->H_oe;
+    bool try_s = true, try_o = c->oe != FAM_OE_OFF;
     for (int H : cand) {
-      if (H > ny) continue;
-      r = set_stage_H(c, H);
-      if (r != FAM_OK) return r;
-      c->H_oe = H;
+      if (H > ny) break;
       float ms = 0.0f;
-      r = time_launches(c, reps, [&] { enqueue_stage(c, 1, 0, U, U, c->W1, nullptr); }, &ms);
-      if (r != FAM_OK) return r;
-      if (ms < best_s) { best_s = ms; hs = H; }
-      if (c->oe != FAM_OE_OFF) {
+      if (try_s) {
+        r = set_stage_H(c, H);
+        if (r != FAM_OK) return r;
+        r = time_launches(c, reps, [&] { enqueue_stage(c, 1, 0, U, U, c->W1, nullptr); }, &ms);
+        if (r != FAM_OK) return r;
+        if (ms < best_s) { best_s = ms; hs = H; }
+        try_s = ms < TUNE_STOP * best_s;
+      }
+      if (try_o) {
+        c->H_oe = H;
         r = time_launches(c, reps, [&] { enqueue_oe(c, 0, U, c->W2, nullptr); }, &ms);
         if (r != FAM_OK) return r;
         if (ms < best_o) { best_o = ms; ho = H; }
+        try_o = ms < TUNE_STOP * best_o;
       }
     }
     // limiter on: the cost-partitioned segment list (reported as height 0)
@@ -733,6 +746,7 @@ extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* c
       r = build_work_list(c, H);
       if (r != FAM_OK) return r;
       const int candP[] = {1024, 2048, 4096, c->nwork};
+      float here = 1e30f;   // the height's fastest grid
       for (int P : candP) {
         c->pblocks = std::max(1, std::min(P, c->nwork));
         float ms = 0.0f;
@@ -741,8 +755,10 @@ extern "C" fam_status fam_autotune(fam_ctx* c, const double* U, int reps, int* c
           if (c->oe != FAM_OE_OFF) enqueue_oe(c, 0, U, c->W2, nullptr);
         }, &ms);
         if (r != FAM_OK) return r;
+        here = std::min(here, ms);
         if (ms < best) { best = ms; bh = H; bp = c->pblocks; }
       }
+      if (here > TUNE_STOP * best) break;
     }
     r = build_work_list(c, bh);
     if (r != FAM_OK) return r;
