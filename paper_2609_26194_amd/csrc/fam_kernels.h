@@ -31,11 +31,10 @@ inline bool starts_at_once(int nblocks, int nitems, int waves) {
 // on a SIMD take 1 + share (w - 1) times as long as one, up to `waves` of them,
 // and further tiles follow in rounds.  On small meshes the rows' latency decides:
 // one-row tiles on every SIMD; from about a million cells it is the ring rows and
-// the last round.  Measured (us a stage launch at the model's height against the 8
-// rows that were the least before): 40x40 k=4 10.7 / 37.6; 96x80 k=5, limiter 23.5
-// / 64.8; 203x131 k=5 14.3 / 47.6; 256x256 k=6 22.8 / 58.2; 512x512 k=5 37.7 /
-// 52.2 (5 rows); 700x700 k=5 56.9 / 79.8 (5 rows); 1024x1024 k=5 110.7 / 129.9
-// (10 rows); 1201x1000 k=6 167.5 / 180.9 (24 rows).
+// the last round.  Measured (us a stage launch at the model's height / with 8 rows):
+// 40x40 k=4 10.7 / 37.6; 96x80 k=5, limiter 23.5 / 64.8; 203x131 k=5 14.3 / 47.6;
+// 256x256 k=6 22.8 / 58.2; 512x512 k=5 37.7 / 52.2 (5 rows); 700x700 k=5 56.9 / 79.8
+// (5 rows); 1024x1024 k=5 110.7 / 129.9 (10 rows); 1201x1000 k=6 167.5 / 180.9 (24).
 template <class F>
 inline int model_rows(F tiles, int ny, int waves, double share) {
   int best = 1;

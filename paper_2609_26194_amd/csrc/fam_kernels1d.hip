@@ -641,7 +641,7 @@ void launch_stage1d(int k, int sys, const StageArgs& A, const Inst& in, hipStrea
   }
   FAM_DISPATCH_P1(sys, FAM_DISPATCH_K1(k, hipLaunchKernelGGL((stage1d_kernel<KK, PP>), grid, dim3(T1), 0, s, A, in)));
 }
-// steps of a mesh that run1d_fits; fresh: the first of a run (its books start anew)
+// steps of a mesh of up to run1d_max cells; fresh: the first of a run (its books start anew)
 void launch_run1d(int k, int sys, const PhysParams& pp, double* U, const Inst& in, StepState* st, int* flag,
                   int nsteps, int test, bool more, bool fresh, double dt_fixed, double t_final, int oe,
                   double gamma_k, hipStream_t s) {

@@ -293,7 +293,7 @@ constexpr int POINTS_MIN = 6, POINTS_CELLS = 4;
 
 // ---------------------------------------------------------------------------
 // Registers and LDS of a stage wave.  What bounds the kernel is the issue of vector
-// instructions (about 2150 per row of 64 cells at k = 5, 1670 of them FP64), so it
+// instructions (2143 per row of 64 cells at k = 5, 1885 of them FP64), so it
 // is written for few of them and for a second wave on the SIMD to fill the gaps:
 // two waves have 256 registers and 20 KB of LDS each.  The rows of k = 3..5 fit without
 // spilling (k = 5: 120 registers of coefficients, 40 carried from row to row), because
@@ -807,11 +807,11 @@ __device__ __forceinline__ void centre_values(const double (&u0)[9], const doubl
 }
 
 // What bounds it: from a million cells instruction issue and the bytes alike (read 12
-// planes, write 8, against some 860 instructions a row at k = 5, 1350 before the even and
+// planes, write 8, against 789 instructions a row at k = 5, 998 before the even and
 // odd parts), on smaller meshes the rows' latency.  k = 5, us a launch before and after:
-// 2048x2048 200 / 183, 1400x1400 103 / 86 (floors at the copy rate 133 and 62), a batch
-// of 40 meshes 183 / 167.  A row's reads of LDS come first; then the row above the next one is
-// loaded into the slot of the row below, past the vector registers, while this row's
+// 2048x2048 200 / 185 on average over a run and 157 at the least, 1400x1400 103 / 86
+// (floors at the copy rate 133 and 62), a batch of 40 meshes 183 / 167.  A row's reads
+// of LDS come first; then the row above the next one is loaded into the slot of the row below, past the vector registers, while this row's
 // jumps and the factors of the row below are computed.  Where no more waves could run
 // for it, a fourth slot takes that row from the start of the iteration on (scalar
 // equations, and launches of at most one wave per SIMD; with two per SIMD three slots of
